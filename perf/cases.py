@@ -61,7 +61,7 @@ def listed():
              depth=12, rows=20_001, layout="blocked", launch="default", ld_pad=16, missing=0.0),
         # the large tabular workload: a forest beyond the last-level cache,
         # walked in passes, with its preset
-        dict(name="tabular_2m", kind="predict", data="tabular", features=28, classes=2, trees=96, train=400_000,
+        dict(name="tabular_2m", kind="predict", data="tabular", features=28, classes=2, trees=160, train=400_000,
              depth=0, rows=2_000_000, layout="preset", launch="preset", ld_pad=0, missing=0.0),
         # many uneven forests in one graph launch
         dict(name="plan_16", kind="plan", jobs=16, trees=512, features=256, train=10_000, depth=12, rows=60_000),
