@@ -214,8 +214,10 @@ int fp_packed_info_get(const fp_packed *p, fp_packed_info *out);
 int fp_packed_host_bytes(const fp_packed *p, const void **bytes, size_t *nbytes);
 
 /* Rebuild a packed forest from bytes written by fp_packed_host_bytes or
- * fp_packed_save.  Verifies magic, version, sizes, checksum and every node
- * reference; FP_ECORRUPT on any mismatch.  The bytes are copied. */
+ * fp_packed_save.  Verifies magic, version, sizes, checksum, every node
+ * reference, that bins of blocks do not overlap and that a CLUSTERED block's
+ * exits are the leaves of one tree; FP_ECORRUPT on any mismatch.  The bytes
+ * are copied. */
 int fp_packed_from_bytes(const void *bytes, size_t nbytes, fp_packed **out);
 
 int fp_packed_save(const fp_packed *p, const char *path);
@@ -225,6 +227,9 @@ int fp_packed_load(const char *path, fp_packed **out);
  * Copy the packed buffer to device memory `dev` (at least info.bytes bytes,
  * 256-byte aligned, owned by the caller and kept alive while p is used) on
  * `stream`.  p remembers dev and the current device; predictions read it.
+ * Block layouts are put into a form made for the walk there (same splits,
+ * fewer bytes; inside info.bytes): the device copy is for predictions only,
+ * the packed format is what the host functions return.
  * Errors: FP_EINVAL (null, misaligned), FP_E2BIG (cap too small), FP_EHIP.
  */
 int fp_packed_upload(fp_packed *p, void *dev, size_t cap, void *stream);

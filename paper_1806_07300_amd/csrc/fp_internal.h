@@ -177,6 +177,74 @@ struct Header {
 };
 static_assert(sizeof(Header) == 256, "header is 256 bytes");
 
+// The walk form of a block.  fp_packed_upload rewrites the device copy's
+// blocks (walk_form_kernel), each bin in place, so that a step of the walk
+// loads few 16-byte pieces and decodes them with few instructions: a lane's
+// piece costs the vector memory path 0.74 cycles from L1 whatever the lines
+// (64-byte blocks 2.9 cycles a lane, 48-byte ones 2.2; from L2 2.4 to 2.9),
+// which bounds the walk long before bandwidth does.
+//  * exits in left-to-right order, and per slot a kill mask: the exits of its
+//    left subtree.  Every slot whose test goes right kills its mask; the exit
+//    taken is the lowest one alive (all exits left of it hang below a node of
+//    its path that went right, and no test kills it).  Exit 7 is never killed;
+//  * slots in left-to-right order too (slot i between exits i and i + 1): the
+//    mask of slot i ends in bit i, so only the i bits below are stored, one
+//    field after the other (21 bits).  Slots and exits beyond a smaller
+//    block's own repeat its last exit, so their tests decide nothing;
+//  * a target per exit: a class with the leaf bit set, or the rank in the
+//    child group;
+//  * base: the first child block as a walk reference (below).
+// A walk reference is kGlobalRef + the block's place in the node section, or,
+// below kGlobalRef, in LDS (both in WalkShape::unit bytes): a workgroup that
+// copies a bin's first blocks to LDS rewrites the base of the copied blocks
+// whose children it copied too (stage_group), so a reference itself says
+// where its block lies.  Dwords of a block (fields from the low bit up):
+//   kWalk32h  0-2, low half of 3: fp16 thr; high half of 3: masks 1..5; 4, 5:
+//             9-bit features 0..2, 3..5 and in their upper five bits the low
+//             and high part of feature 6; 6 and the low byte of 7: targets in
+//             5 bits; 7: base in bits [8, 28), start of mask 6 in [28, 31)
+//   kWalk48f  0-6 thr; 7, 8: 10-bit features 0..2, 3..5; 9: feature 6, masks
+//             1..6 in [10, 31); 10: targets in 4 bits; 11: base
+//   kWalk48b  0-6 thr; 7, 8: 10-bit features 0..2, 3..5; 9 base; 10, low half
+//             of 11: targets in 6 bits; high half of 11: feature 6.  BLOCKED
+//             blocks are complete three-level subtrees: constant masks
+//   kWalk48h  0-3 fp16 thr (7 halves), feature 6; 4-6 features 0..5, 16 bits;
+//             7 mask bytes 0..3, 8 base, 9-10 targets in 8 bits, 11 mask
+//             bytes 4..6
+//   kWalk64   0-6 thr, 7-8 mask bytes, 9-12 16-bit features, 13-14 targets in
+//             8 bits, 15 base
+// kWalkNone: the host form is walked as it is (run_tile_blocked).
+enum WalkForm : int32_t { kWalkNone = 0, kWalk64, kWalk48h, kWalk48b, kWalk48f, kWalk32h };
+constexpr int32_t kGlobalRef = 1 << 14;  // above any LDS address in 16-byte units (160 KB)
+
+struct WalkShape {
+    int32_t bytes;  // of a block
+    int32_t unit;   // bytes a walk reference counts
+    uint32_t leaf;  // the leaf bit of a target
+    int32_t tbits;  // bits of a target
+};
+constexpr WalkShape walk_shape(int32_t form) {
+    return form == kWalk32h   ? WalkShape{32, 32, 16u, 5}
+           : form == kWalk48f ? WalkShape{48, 16, 8u, 4}
+           : form == kWalk48b ? WalkShape{48, 16, 32u, 6}
+           : form == kWalk48h ? WalkShape{48, 16, 128u, 8}
+                              : WalkShape{64, 16, 128u, 8};
+}
+
+// The walk form fp_packed_upload gives the device copy of a forest: the
+// smallest whose fields hold its classes, features and (kWalk32h: 20 bits)
+// references.  Every CLUSTERED forest has one; a BLOCKED one with more than
+// 32 classes (48-byte form) or 128, or more features than fit, has none.
+inline int32_t walk_form(const Header& h) {
+    const int64_t section = h.total_bytes - h.nodes_offset;
+    if (h.layout == FP_LAYOUT_CLUSTERED && h.block_bytes == 48)
+        return h.n_classes <= 16 && section / 32 < (1 << 20) - kGlobalRef ? kWalk32h : kWalk48h;
+    if (h.layout != FP_LAYOUT_CLUSTERED && h.layout != FP_LAYOUT_BLOCKED) return kWalkNone;
+    if (h.block_bytes == 48) return h.n_classes <= 32 && h.n_used_features <= 1024 ? kWalk48b : kWalkNone;
+    if (h.n_classes <= 8 && h.n_used_features <= 1024) return kWalk48f;
+    return h.n_classes <= 128 && h.n_used_features <= 65535 ? kWalk64 : kWalkNone;
+}
+
 uint64_t fnv1a64(const uint8_t* p, size_t n);
 
 // Verifies header fields, section bounds, checksum and every reference.
@@ -214,7 +282,7 @@ struct JobDesc {
     int32_t layout;            // FP_LAYOUT_PACKED, FP_LAYOUT_COMPACT or FP_LAYOUT_BLOCKED
     int32_t fbits, cbits;      // COMPACT / BLOCKED field widths
     int32_t refill_min;        // idle lanes of a wavefront that trigger a refill
-    int32_t block_bytes;       // BLOCKED: 48 or 64
+    int32_t block_bytes;       // block layouts: bytes of a block as the kernel reads it
     int32_t F;                 // feature columns of a row (the forest's n_features)
     int32_t stage_rows;        // 1: stage tiles with whole-row 16-byte loads through imap
     int32_t off_imap;          // LDS: column -> compacted feature (int16, -1 unused), 4 * ceil(F / 4) entries
@@ -222,7 +290,8 @@ struct JobDesc {
     int32_t passes;            // consecutive launches over the groups (tree_passes), 1 in batched launches
     int32_t group_base;        // first group of this launch: workgroup b walks group group_base + b % G
     int32_t accumulate;        // 1: add the tile's votes to the stored ones (a later pass)
-    int32_t pad_job;
+    int32_t form;              // WalkForm of the device copy's blocks
+    int32_t n_trees, pad_job;
 };
 
 // A job whose groups run in several passes, flattened for launches where all
@@ -264,7 +333,7 @@ int resolve_job(const fp_packed* p, const fp_tune* t, const float* X, int64_t n_
 // Default LDS footprint of one workgroup: what keeps two workgroups per CU.
 size_t default_lds_block(const DeviceProps& dp);
 
-int packed_occupancy(int K, int fmode, int layout, int threads, size_t lds, int* blocks_per_cu);
+int packed_occupancy(int K, const JobDesc& j, int threads, int* blocks_per_cu);
 // Batched launches: `lds` is the largest job layout; the launch adds a
 // 16-byte slot after it (the workgroup's item number), so jobs are resolved
 // against batched_job_budget(lds_block).
@@ -282,8 +351,9 @@ int batched_occupancy(int K, bool blocks_only, int threads, size_t lds, int* blo
 bool jobs_blocks_only(const JobDesc* jobs, int32_t n_jobs);
 
 // The packer's two device operations, kept out of the host-only packer:
-// copy n bytes to device memory on `stream` and wait for it (the current
-// device's id in *dev_id), and count on the GPU the rows of X that end in
+// copy a packed buffer of n bytes to device memory on `stream`, put its
+// blocks into their walk form there and wait for it (the current device's id
+// in *dev_id), and count on the GPU the rows of X that end in
 // each leaf of a NAIVE-layout buffer (`bytes`, header h), node by node of
 // that buffer into counts[h.n_nodes] (host), synchronising `stream`.
 int device_upload(void* dev, const void* src, size_t n, void* stream, int* dev_id);

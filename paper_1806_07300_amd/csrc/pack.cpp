@@ -996,6 +996,7 @@ int verify_buffer(const uint8_t* bytes, size_t n, std::string* why) {
     const int32_t* roots = reinterpret_cast<const int32_t*>(bytes + h.roots_offset);
     int32_t tree_cursor = 0;
     int32_t max_top = 0, max_trees = 0;
+    int64_t blocks_end = 0;
     for (int32_t b = 0; b < h.n_bins; b++) {
         const BinEntry& be = bins[b];
         if (be.first_tree != tree_cursor || be.n_trees < 1 || be.root_base != be.first_tree)
@@ -1007,6 +1008,9 @@ int verify_buffer(const uint8_t* bytes, size_t n, std::string* why) {
         if (be.top_len < 0 || be.deep_len < 0 || be.node_base < 0 || be.node_base % (compact || blocked ? 16 : 8) ||
             be.node_base + units > N)
             return bad("bin %d node range", b);
+        // blocks are rewritten in place on the device, bin by bin
+        if (blocked && be.node_base < blocks_end) return bad("bin %d overlaps the bins before it", b);
+        if (blocked) blocks_end = be.node_base + units;
         const int64_t len = (int64_t)be.top_len + be.deep_len;
         max_top = std::max(max_top, be.top_len);
         max_trees = std::max(max_trees, be.n_trees);
@@ -1096,9 +1100,14 @@ int verify_buffer(const uint8_t* bytes, size_t n, std::string* why) {
                             return bad("bin %d block %lld exit %u class", b, (long long)k, e);
                         }
                         covered += (int64_t)1 << (n_slot - __builtin_popcount(care));
-                        for (uint32_t d = 0; d < e; d++)
-                            if (((val ^ bk.val[d]) & care & bk.care[d]) == 0)
-                                return bad("bin %d block %lld exits %u and %u overlap", b, (long long)k, d, e);
+                        // ... and are the leaves of one tree over the slots: two exits
+                        // part at one slot (the walk form orders them by it)
+                        for (uint32_t d = 0; d < e; d++) {
+                            const uint32_t part = (val ^ bk.val[d]) & care & bk.care[d];
+                            if (part == 0) return bad("bin %d block %lld exits %u and %u overlap", b, (long long)k, d, e);
+                            if (part & (part - 1))
+                                return bad("bin %d block %lld exits %u and %u part at several slots", b, (long long)k, d, e);
+                        }
                     }
                     if (covered != ((int64_t)1 << n_slot) || child_used != (n_child ? (1u << n_child) - 1u : 0u))
                         return bad("bin %d block %lld: exits do not cover every outcome once", b, (long long)k);

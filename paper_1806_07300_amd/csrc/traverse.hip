@@ -227,29 +227,82 @@ __device__ __forceinline__ void put_feature(void* row, int c, float v, uint32_t 
     else static_cast<float*>(row)[c] = v;
 }
 
+// Rows of the tile that starts at row0.
+__device__ __forceinline__ int tile_rows(const JobDesc& j, int64_t row0) { return (int)min<int64_t>(j.R, j.n_rows - row0); }
+
+// Whole-row staging: quad (four columns) qd of row r goes to thread
+// (r Q + qd) mod blockDim.  The thread's first quad of a tile, issued ahead
+// of the staging of its group so that the two wait for memory together;
+// stage_tile takes it over.
+template <int FMODE>
+__device__ __forceinline__ float4 prefetch_quad(const JobDesc& j, int tile) {
+    float4 v = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+    if (FMODE != 1 || !j.stage_rows || tile >= j.n_tiles) return v;
+    const int Q = (j.F + 3) / 4, r = (int)threadIdx.x / Q, qd = (int)threadIdx.x - r * Q;
+    const int64_t row0 = (int64_t)tile * j.R;
+    if (r < tile_rows(j, row0)) v = reinterpret_cast<const float4*>(j.X + (row0 + r) * j.ld)[qd];
+    return v;
+}
+
 // Copies the used feature columns of tile rows [row0, row0 + rows) into LDS
 // (fp32 row-major, row stride Fcp; or, when X16, fp16 feature-major, feature
 // stride Fcp, so that lanes reading one feature of consecutive rows share
 // LDS words), clears
-// the tile's vote counters and the unit pool, then synchronises.  Element
-// i = r * Fc + c goes to thread i mod blockDim, which steps (r, c) and the
-// row pointer incrementally.
+// the tile's vote counters and the unit pool, then synchronises.  kStageBatch
+// independent 16-byte loads of a thread are in flight before their scatter.
+// prefetched: the thread's first quad is `pre`.
 template <bool X16 = false>
 __device__ __forceinline__ void stage_tile(const JobDesc& j, float* xs, int32_t* vl, int32_t* pool, int64_t row0,
-                                           int rows, bool feat_lds) {
+                                           int rows, bool feat_lds, float4 pre, bool prefetched) {
     const int tid = threadIdx.x, bd = blockDim.x;
+    for (int i = tid; i < rows * j.C; i += bd) vl[i] = 0;
+    if (tid == 0) *pool = 0;
     if (feat_lds && j.stage_rows) {
         // whole rows in 16-byte loads; each used column goes to its compacted
-        // slot (imap, 4 entries per 8-byte LDS read; -1 = unused)
-        const int Q = (j.F + 3) / 4;
+        // slot (imap, 4 entries per 8-byte LDS read; -1 = unused), or, when
+        // every column is used, to its own place
         const int16_t* imap = reinterpret_cast<const int16_t*>(reinterpret_cast<const unsigned char*>(xs) - j.off_xs +
                                                                j.off_imap);
+        auto scatter = [&](int r, int qd, float4 v) {
+            int m0 = 4 * qd, m1 = m0 + 1, m2 = m0 + 2, m3 = m0 + 3;
+            if (j.Fc < j.F) {
+                const int2 m = *reinterpret_cast<const int2*>(imap + m0);
+                m0 = (int16_t)(m.x & 0xFFFF);
+                m1 = m.x >> 16;
+                m2 = (int16_t)(m.y & 0xFFFF);
+                m3 = m.y >> 16;
+            } else if (m3 >= j.F) {  // the last quad of a row: columns past the features
+                m1 = m1 < j.F ? m1 : -1;
+                m2 = m2 < j.F ? m2 : -1;
+                m3 = -1;
+            }
+            // fp32: row r, element m; fp16: element m * Fcp of row r
+            void* dst = X16 ? static_cast<void*>(reinterpret_cast<uint16_t*>(xs) + r) : static_cast<void*>(xs + r * j.Fcp);
+            const int es = X16 ? j.Fcp : 1;
+            uint32_t h[4] = {0, 0, 0, 0};
+            if constexpr (X16) half_up4(v.x, v.y, v.z, v.w, h);
+            if (m0 >= 0) put_feature<X16>(dst, m0 * es, v.x, h[0]);
+            if (m1 >= 0) put_feature<X16>(dst, m1 * es, v.y, h[1]);
+            if (m2 >= 0) put_feature<X16>(dst, m2 * es, v.z, h[2]);
+            if (m3 >= 0) put_feature<X16>(dst, m3 * es, v.w, h[3]);
+        };
+        const int Q = (j.F + 3) / 4;
         const int dq = bd / Q, dc = bd - dq * Q;
         int r = tid / Q, qd = tid - r * Q;
-        const float4* xrow = reinterpret_cast<const float4*>(j.X + (row0 + r) * j.ld);
-        const int64_t ld4 = j.ld / 4, dld4 = (int64_t)dq * ld4;
-        // kStageBatch independent 16-byte loads in flight per thread, then
-        // their scatter into the compacted columns
+        auto step = [&]() {  // to the thread's next quad
+            r += dq;
+            qd += dc;
+            if (qd >= Q) {
+                qd -= Q;
+                r += 1;
+            }
+        };
+        if (prefetched) {
+            if (r < rows) scatter(r, qd, pre);
+            step();
+        }
+        const int64_t ld4 = j.ld / 4;
+        const float4* x0 = reinterpret_cast<const float4*>(j.X + row0 * j.ld);
         while (r < rows) {
             float4 v[kStageBatch];
             int rr[kStageBatch], qq[kStageBatch];
@@ -257,35 +310,17 @@ __device__ __forceinline__ void stage_tile(const JobDesc& j, float* xs, int32_t*
             for (int u = 0; u < kStageBatch; u++) {
                 rr[u] = r;
                 qq[u] = qd;
-                if (r < rows) v[u] = xrow[qd];
-                r += dq;
-                xrow += dld4;
-                qd += dc;
-                if (qd >= Q) {
-                    qd -= Q;
-                    r += 1;
-                    xrow += ld4;
-                }
+                if (r < rows) v[u] = x0[r * ld4 + qd];
+                step();
             }
 #pragma unroll
             for (int u = 0; u < kStageBatch; u++) {
                 if (rr[u] >= rows) break;
-                const int2 m2 = *reinterpret_cast<const int2*>(imap + 4 * qq[u]);
-                const int m0 = (int16_t)(m2.x & 0xFFFF), m1 = m2.x >> 16, m2v = (int16_t)(m2.y & 0xFFFF),
-                          m3 = m2.y >> 16;
-                // fp32: row rr, element m; fp16: element m * Fcp of row rr
-                void* dst = X16 ? static_cast<void*>(reinterpret_cast<uint16_t*>(xs) + rr[u])
-                                : static_cast<void*>(xs + rr[u] * j.Fcp);
-                const int es = X16 ? j.Fcp : 1;
-                uint32_t h[4] = {0, 0, 0, 0};
-                if constexpr (X16) half_up4(v[u].x, v[u].y, v[u].z, v[u].w, h);
-                if (m0 >= 0) put_feature<X16>(dst, m0 * es, v[u].x, h[0]);
-                if (m1 >= 0) put_feature<X16>(dst, m1 * es, v[u].y, h[1]);
-                if (m2v >= 0) put_feature<X16>(dst, m2v * es, v[u].z, h[2]);
-                if (m3 >= 0) put_feature<X16>(dst, m3 * es, v[u].w, h[3]);
+                scatter(rr[u], qq[u], v[u]);
             }
         }
     } else if (feat_lds) {
+        // element i = r * Fc + c goes to thread i mod blockDim
         const int Fc = j.Fc;
         const int dq = bd / Fc, dc = bd - dq * Fc;
         int r = tid / Fc, c = tid - r * Fc;
@@ -305,8 +340,6 @@ __device__ __forceinline__ void stage_tile(const JobDesc& j, float* xs, int32_t*
             }
         }
     }
-    for (int i = tid; i < rows * j.C; i += bd) vl[i] = 0;
-    if (tid == 0) *pool = 0;
     __syncthreads();
 }
 
@@ -377,43 +410,142 @@ struct TileRows {
     }
 };
 
+// What a kernel walks: a node layout, blocks in their host form, or blocks in
+// a walk form (with an fp16 tile: X); one kernel each, so that a launch
+// fetches only its own code and the compiler knows the block's shape.
+// kKindAny, kKindAnyBlock: decided per job (batched launches).
+enum Kind : int {
+    kKindPacked, kKindCompact, kKindHost48, kKindHost64, kKind64, kKind48h, kKind48hX, kKind48b, kKind48f, kKind32h,
+    kKind32hX, kKindAny, kKindAnyBlock
+};
+constexpr int32_t kind_form(int kind) {
+    return kind == kKind64                           ? (int32_t)fp::kWalk64
+           : kind == kKind48h || kind == kKind48hX   ? (int32_t)fp::kWalk48h
+           : kind == kKind48b                        ? (int32_t)fp::kWalk48b
+           : kind == kKind48f                        ? (int32_t)fp::kWalk48f
+           : kind == kKind32h || kind == kKind32hX   ? (int32_t)fp::kWalk32h
+                                                     : (int32_t)fp::kWalkNone;
+}
+__host__ __device__ __forceinline__ int job_kind(const JobDesc& j) {
+    return j.layout == FP_LAYOUT_COMPACT       ? kKindCompact
+           : j.layout < FP_LAYOUT_BLOCKED      ? kKindPacked
+           : j.form == fp::kWalk64             ? kKind64
+           : j.form == fp::kWalk48h            ? (j.x16 ? kKind48hX : kKind48h)
+           : j.form == fp::kWalk48b            ? kKind48b
+           : j.form == fp::kWalk48f            ? kKind48f
+           : j.form == fp::kWalk32h            ? (j.x16 ? kKind32hX : kKind32h)
+           : j.block_bytes == 48               ? kKindHost48
+                                               : kKindHost64;
+}
+
+// LDS and global pointers are typed with their address spaces so that the
+// compiler keeps an LDS read and a global load apart rather than merging them
+// into one flat load through a selected pointer.
+typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+typedef __attribute__((address_space(3))) const u32x4 lds_u32x4;
+typedef __attribute__((address_space(1))) const u32x4 global_u32x4;
+
+__device__ __forceinline__ uint4 as_uint4(u32x4 v) { return make_uint4(v.x, v.y, v.z, v.w); }
+
+// LDS byte address of a pointer into the workgroup's shared memory, and back.
+__device__ __forceinline__ uint32_t lds_addr(const void* p) {
+    return (uint32_t)(size_t)(__attribute__((address_space(3))) const void*)p;
+}
+template <typename T>
+__device__ __forceinline__ __attribute__((address_space(3))) const T* lds_ptr(uint32_t a) {
+    return (__attribute__((address_space(3))) const T*)(size_t)a;
+}
+
+
+// The base of a block in a walk form, in the piece that holds it (the last
+// one, with the targets), and that piece with another base.
+__device__ __forceinline__ uint32_t piece_base(int32_t form, const uint4& p) {
+    return form == fp::kWalk32h                          ? (p.w >> 8) & 0xFFFFFu
+           : form == fp::kWalk48h                        ? p.x
+           : form == fp::kWalk48b                        ? p.y
+                                                         : p.w;
+}
+__device__ __forceinline__ void set_piece_base(int32_t form, uint4& p, uint32_t base) {
+    if (form == fp::kWalk32h) p.w = (p.w & ~0x0FFFFF00u) | base << 8;
+    else if (form == fp::kWalk48h) p.x = base;
+    else if (form == fp::kWalk48b) p.y = base;
+    else p.w = base;
+}
 // Stage the bin tops, the tree table and (when features are read from memory)
 // the feature map of tree group `group`; returns the group's tree count.
 // The caller must have synchronised since the previous use of LDS.
-__device__ int stage_group(const JobDesc& j, int group, unsigned char* smem) {
+template <int KIND>
+__device__ __forceinline__ int stage_group(const JobDesc& j, int group, unsigned char* smem) {
     const int tid = threadIdx.x, bd = blockDim.x;
     const int b_lo = group * j.bins_per_group;
     const int b_hi = min(b_lo + j.bins_per_group, j.n_bins);
     if (b_lo >= b_hi) return 0;
-    Node16* top = reinterpret_cast<Node16*>(smem + j.off_top);
+    uint4* top = reinterpret_cast<uint4*>(smem + j.off_top);
     int4* ttab = reinterpret_cast<int4*>(smem + j.off_ttab);
-    const int t_lo = j.bins[b_lo].first_tree;
-    const int nt = j.bins[b_hi - 1].first_tree + j.bins[b_hi - 1].n_trees - t_lo;
-    // PACKED: the bin's top nodes; BLOCKED: its first blocks (roots first), as
-    // 16-byte pieces; cap pieces per bin
-    const int bw = j.block_bytes / 16;
-    for (int i = tid; i < (b_hi - b_lo) * j.cap; i += bd) {
-        const int bl = i / j.cap, k = i - bl * j.cap;
-        const BinEntry& be = j.bins[b_lo + bl];
-        const bool blk = j.layout >= FP_LAYOUT_BLOCKED;
-        const int32_t have = blk ? be.deep_len * bw : be.top_len;
-        if (k < have) top[i] = j.nodes[(blk ? be.node_base / 2 : be.node_base) + k];
+    const int t_lo = b_lo * j.bin_size;
+    const int nt = (int)min((int64_t)b_hi * j.bin_size, (int64_t)j.n_trees) - t_lo;
+    constexpr bool any = KIND == kKindAny || KIND == kKindAnyBlock;
+    const bool blk = KIND == kKindAny ? j.layout >= FP_LAYOUT_BLOCKED : KIND != kKindPacked && KIND != kKindCompact;
+    const int32_t form = any ? j.form : kind_form(KIND);
+    // PACKED: the bin's top nodes; block layouts: its first blocks (roots
+    // first), as 16-byte pieces; cap pieces per bin
+    const int bw = !blk ? 1 : any || form == fp::kWalkNone ? j.block_bytes / 16 : fp::walk_shape(form).bytes / 16;
+    const int per = form == fp::kWalk32h ? 2 : 1;  // pieces a walk reference counts
+    // Each table's loads are issued a round ahead: the first round's (tree
+    // roots, their bins, the pieces' bins) go out together before any is used.
+    const int pieces = (b_hi - b_lo) * j.cap;
+    const uint32_t capm = 0xFFFFFFFFu / (uint32_t)max(j.cap, 1), binm = 0xFFFFFFFFu / (uint32_t)j.bin_size;
+    uint32_t rem;
+    auto bin_of_piece = [&](int i) { return j.bins[b_lo + (int)div_rows((uint32_t)i, (uint32_t)j.cap, capm, rem)]; };
+    auto bin_of_tree = [&](int tl) { return j.bins[b_lo + (int)div_rows((uint32_t)tl, (uint32_t)j.bin_size, binm, rem)]; };
+    BinEntry pe, te;
+    int32_t root = 0;
+    if (tid < pieces) pe = bin_of_piece(tid);
+    if (tid < nt) {
+        te = bin_of_tree(tid);
+        root = j.roots[t_lo + tid];
+    }
+    for (int i = tid; i < pieces; i += bd) {
+        uint32_t k;
+        const int bl = (int)div_rows((uint32_t)i, (uint32_t)j.cap, capm, k);
+        if (i != tid) pe = bin_of_piece(i);
+        const int32_t have = min(blk ? pe.deep_len * bw : pe.top_len, j.cap);
+        const int64_t first = blk ? pe.node_base / 2 : pe.node_base;
+        if ((int)k >= have) continue;
+        uint4 p = reinterpret_cast<const uint4*>(j.nodes)[first + k];
+        if (form != fp::kWalkNone && (int)k % bw == bw - 1) {
+            // a child group (up to eight blocks) that is copied too is named by its LDS address
+            const int32_t child = ((int32_t)piece_base(form, p) - fp::kGlobalRef - (int32_t)(first / per)) * per;
+            if (child + 8 * bw <= have)
+                set_piece_base(form, p, (lds_addr(top) / 16u + (uint32_t)(bl * j.cap + child)) / (uint32_t)per);
+        }
+        top[i] = p;
     }
     for (int tl = tid; tl < nt; tl += bd) {
-        const int t = t_lo + tl;
-        const int b = t / j.bin_size;
-        const BinEntry& be = j.bins[b];
-        const int32_t nb = (int32_t)be.node_base;
-        ttab[tl] = j.layout == FP_LAYOUT_COMPACT   ? make_int4(j.roots[t], nb, be.top_len, 0)
-                   : j.layout >= FP_LAYOUT_BLOCKED ? make_int4(j.roots[t], nb, (b - b_lo) * j.cap,
-                                                               min(be.deep_len, j.cap / max(bw, 1)))
-                                                   : make_int4(j.roots[t], nb, (b - b_lo) * j.cap, min(be.top_len, j.cap));
+        if (tl != tid) {
+            te = bin_of_tree(tl);
+            root = j.roots[t_lo + tl];
+        }
+        const int bl = (int)div_rows((uint32_t)tl, (uint32_t)j.bin_size, binm, rem);
+        const int32_t nb = (int32_t)te.node_base;
+        if (form != fp::kWalkNone) {
+            const int32_t at = root * bw;
+            reinterpret_cast<int32_t*>(ttab)[tl] =
+                root < 0                                  ? root
+                : at + bw <= min(te.deep_len * bw, j.cap) ? ((int32_t)(lds_addr(top) / 16u) + bl * j.cap + at) / per
+                                                          : fp::kGlobalRef + (int32_t)((te.node_base / 2 + at) / per);
+            continue;
+        }
+        ttab[tl] = (any ? j.layout == FP_LAYOUT_COMPACT : KIND == kKindCompact)
+                       ? make_int4(root, nb, te.top_len, 0)
+                   : blk ? make_int4(root, nb, bl * j.cap, min(te.deep_len, j.cap / max(bw, 1)))
+                         : make_int4(root, nb, bl * j.cap, min(te.top_len, j.cap));
     }
     if (!j.feat_lds) {
         int32_t* fmap_l = reinterpret_cast<int32_t*>(smem + j.off_fmap);
         for (int c = tid; c < j.Fc; c += bd) fmap_l[c] = j.fmap[c];
     }
-    if (j.stage_rows) {
+    if (j.stage_rows && j.Fc < j.F) {
         int16_t* imap = reinterpret_cast<int16_t*>(smem + j.off_imap);
         const int n_imap = (j.F + 3) / 4 * 4;
         for (int c = tid; c < n_imap; c += bd) imap[c] = -1;
@@ -426,7 +558,7 @@ __device__ int stage_group(const JobDesc& j, int group, unsigned char* smem) {
 
 // FMODE: 0 features from memory, 1 features in LDS, 2 decided by j.feat_lds.
 template <int K, int FMODE>
-__device__ void run_tile(const JobDesc& j, int nt, int tile, unsigned char* smem) {
+__device__ __forceinline__ void run_tile(const JobDesc& j, int nt, int tile, unsigned char* smem) {
     const bool feat_lds = FMODE == 2 ? (j.feat_lds != 0) : (FMODE == 1);
     const Node16* top = reinterpret_cast<const Node16*>(smem + j.off_top);
     const int4* ttab = reinterpret_cast<const int4*>(smem + j.off_ttab);
@@ -437,8 +569,7 @@ __device__ void run_tile(const JobDesc& j, int nt, int tile, unsigned char* smem
     const int lane = lane_id();
 
     const int64_t row0 = (int64_t)tile * j.R;
-    const int rows_here = (int)min<int64_t>(j.R, j.n_rows - row0);
-    stage_tile(j, xs, vl, pool, row0, rows_here, feat_lds);
+    const int rows_here = tile_rows(j, row0);
 
     const int U = rows_here * nt;
     const uint32_t rmagic = 0xFFFFFFFFu / (uint32_t)rows_here;
@@ -493,7 +624,7 @@ __device__ void run_tile(const JobDesc& j, int nt, int tile, unsigned char* smem
 typedef uint32_t u32x4_a8 __attribute__((ext_vector_type(4), aligned(8)));
 
 template <int K, int FMODE>
-__device__ void run_tile_compact(const JobDesc& j, int nt, int tile, unsigned char* smem) {
+__device__ __forceinline__ void run_tile_compact(const JobDesc& j, int nt, int tile, unsigned char* smem) {
     const bool feat_lds = FMODE == 2 ? (j.feat_lds != 0) : (FMODE == 1);
     const int4* ttab = reinterpret_cast<const int4*>(smem + j.off_ttab);
     const int32_t* fmap_l = reinterpret_cast<const int32_t*>(smem + j.off_fmap);
@@ -506,8 +637,7 @@ __device__ void run_tile_compact(const JobDesc& j, int nt, int tile, unsigned ch
     const uint32_t fmask = (1u << fb) - 1u, cmask = (1u << cb) - 1u;
 
     const int64_t row0 = (int64_t)tile * j.R;
-    const int rows_here = (int)min<int64_t>(j.R, j.n_rows - row0);
-    stage_tile(j, xs, vl, pool, row0, rows_here, feat_lds);
+    const int rows_here = tile_rows(j, row0);
 
     const int U = rows_here * nt;
     const uint32_t rmagic = 0xFFFFFFFFu / (uint32_t)rows_here;
@@ -597,27 +727,9 @@ struct BlockView {
     uint32_t child_base, ranks;
 };
 
-// Fetches block `ref` of the bin starting at word bb: three (48-byte form) or
-// four (64-byte form) 16-byte loads of one line, issued back to back; the
-// bin's first `ns` blocks come from their LDS copy at piece lb instead.
-// The two sources are typed with their address spaces so that the compiler
-// keeps an LDS read and a global load rather than merging them into one flat
-// load through a selected pointer.
-typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
-typedef __attribute__((address_space(3))) const u32x4 lds_u32x4;
-typedef __attribute__((address_space(1))) const u32x4 global_u32x4;
-
-__device__ __forceinline__ uint4 as_uint4(u32x4 v) { return make_uint4(v.x, v.y, v.z, v.w); }
-
-// LDS byte address of a pointer into the workgroup's shared memory, and back.
-__device__ __forceinline__ uint32_t lds_addr(const void* p) {
-    return (uint32_t)(size_t)(__attribute__((address_space(3))) const void*)p;
-}
-template <typename T>
-__device__ __forceinline__ __attribute__((address_space(3))) const T* lds_ptr(uint32_t a) {
-    return (__attribute__((address_space(3))) const T*)(size_t)a;
-}
-
+// Fetches block `ref` of a bin in its host form: three (48-byte form) or four
+// (64-byte form) 16-byte loads of one line, issued back to back; the bin's
+// first `ns` blocks come from their LDS copy instead.
 // bp = the bin's first block in memory, la = LDS byte address of its copy
 // (blocks below ns).
 template <bool B48>
@@ -666,120 +778,6 @@ __device__ __forceinline__ BlockView view_block(const uint4 (&q)[4]) {
     return b;
 }
 
-// Field [pos, pos + width) of the 160 bits r[0..4] of a CLUSTERED block
-// (positions are compile-time constants, so this is one or two ALU ops).
-template <int pos, int width>
-__device__ __forceinline__ uint32_t cfield(const uint32_t (&r)[5]) {
-    constexpr uint32_t mask = (1u << width) - 1u;
-    if constexpr (pos % 32 + width <= 32) return (r[pos / 32] >> (pos % 32)) & mask;
-    else return __builtin_amdgcn_alignbit(r[pos / 32 + 1], r[pos / 32], pos % 32) & mask;
-}
-
-// Bytes of x that are zero get bit 7 set, the others clear (bytes < 0x80
-// or with bit 7 set; no carry crosses a byte).
-__device__ __forceinline__ uint32_t zero_bytes(uint32_t x) {
-    return ~(((x & 0x7F7F7F7Fu) + 0x7F7F7F7Fu) | x) & 0x80808080u;
-}
-
-// Bits [OFF, OFF + W) of x as one v_bfe_u32 the compiler cannot fold into the
-// address arithmetic that follows (which would cost a shift and a mask).
-template <int OFF, int W>
-__device__ __forceinline__ uint32_t bfe_u32(uint32_t x) {
-    uint32_t r;
-    asm("v_bfe_u32 %0, %1, %2, %3" : "=v"(r) : "v"(x), "i"(OFF), "i"(W));
-    return r;
-}
-
-// Low / high fp16 half of a word widened to fp32 (exact).
-__device__ __forceinline__ float half_lo(uint32_t v) {
-    return (float)__builtin_bit_cast(_Float16, (unsigned short)(v & 0xFFFFu));
-}
-__device__ __forceinline__ float half_hi(uint32_t v) {
-    return (float)__builtin_bit_cast(_Float16, (unsigned short)(v >> 16));
-}
-// The same halves as fp16 values.
-__device__ __forceinline__ _Float16 bits_lo16(uint32_t v) {
-    return __builtin_bit_cast(_Float16, (unsigned short)(v & 0xFFFFu));
-}
-__device__ __forceinline__ _Float16 bits_hi16(uint32_t v) {
-    return __builtin_bit_cast(_Float16, (unsigned short)(v >> 16));
-}
-
-// CLUSTERED block: reads the seven split outcomes (one LDS round trip, as in
-// the BLOCKED walk), tests four exits per 32-bit operation against the
-// outcome mask replicated into every byte, and returns the next reference:
-// the child block or the class of the one exit whose pattern matches.
-// C48: the 48-byte form (fp16 thresholds and 9-bit features); otherwise the
-// 64-byte form.  H16 (48-byte form only): `le` loads a feature of an fp16
-// tile, compared with the fp16 thresholds; else `le` compares with the
-// thresholds widened to fp32.
-template <bool C48, bool H16, typename Le>
-__device__ __forceinline__ int32_t cluster_step(const uint4 (&q)[4], int32_t xrow, Le&& le) {
-    static_assert(C48 || !H16, "fp16 compares need fp16 thresholds");
-    using Thr = std::conditional_t<H16, _Float16, float>;
-    Thr thr[7];
-    uint32_t care_lo, care_hi, val_lo, val_hi, r[5], f[7], child_base, n_child;
-    if constexpr (H16) {
-        thr[0] = bits_lo16(q[0].x); thr[1] = bits_hi16(q[0].x); thr[2] = bits_lo16(q[0].y);
-        thr[3] = bits_hi16(q[0].y); thr[4] = bits_lo16(q[0].z); thr[5] = bits_hi16(q[0].z);
-        thr[6] = bits_lo16(q[0].w);
-    }
-    if constexpr (C48) {
-        if constexpr (!H16) {
-            thr[0] = half_lo(q[0].x); thr[1] = half_hi(q[0].x); thr[2] = half_lo(q[0].y); thr[3] = half_hi(q[0].y);
-            thr[4] = half_lo(q[0].z); thr[5] = half_hi(q[0].z); thr[6] = half_lo(q[0].w);
-        }
-        care_lo = q[1].x; care_hi = q[1].y; val_lo = q[1].z; val_hi = q[1].w;
-        r[0] = q[2].x; r[1] = q[2].y; r[2] = q[2].z; r[3] = q[2].w;
-        static_assert(fp::kC48FeatPos[0] == 48 && fp::kC48FeatPos[1] == 64 && fp::kC48FeatPos[2] == 73 &&
-                          fp::kC48FeatPos[3] == 82 && fp::kC48FeatPos[4] == 96 && fp::kC48FeatPos[5] == 105 &&
-                          fp::kC48FeatPos[6] == 114 && fp::kC48NChildPos == 57 && fp::kC48BasePos == 123,
-                      "field positions below follow the 48-byte block");
-        f[0] = bfe_u32<16, 9>(r[1]);
-        f[1] = bfe_u32<0, 9>(r[2]); f[2] = bfe_u32<9, 9>(r[2]); f[3] = bfe_u32<18, 9>(r[2]);
-        f[4] = bfe_u32<0, 9>(r[3]); f[5] = bfe_u32<9, 9>(r[3]); f[6] = bfe_u32<18, 9>(r[3]);
-        n_child = (r[1] >> 25) & 15u;
-        child_base = __builtin_amdgcn_alignbit(q[0].w >> 16, r[3], 27);  // rest bits [123, 144)
-    } else {
-        thr[0] = __uint_as_float(q[0].x); thr[1] = __uint_as_float(q[0].y); thr[2] = __uint_as_float(q[0].z);
-        thr[3] = __uint_as_float(q[0].w); thr[4] = __uint_as_float(q[1].x); thr[5] = __uint_as_float(q[1].y);
-        thr[6] = __uint_as_float(q[1].z);
-        care_lo = q[1].w; care_hi = q[2].x; val_lo = q[2].y; val_hi = q[2].z;
-        r[0] = q[2].w; r[1] = q[3].x; r[2] = q[3].y; r[3] = q[3].z; r[4] = q[3].w;
-        constexpr int FW = fp::kClusterFeatBits;
-        f[0] = cfield<48, FW>(r); f[1] = cfield<48 + FW, FW>(r); f[2] = cfield<48 + 2 * FW, FW>(r);
-        f[3] = cfield<48 + 3 * FW, FW>(r); f[4] = cfield<48 + 4 * FW, FW>(r); f[5] = cfield<48 + 5 * FW, FW>(r);
-        f[6] = cfield<48 + 6 * FW, FW>(r);
-        n_child = cfield<156, 4>(r);
-        child_base = cfield<132, 24>(r);
-    }
-    uint32_t g = 0;
-    if constexpr (H16) {
-        // all seven features loaded before any compare: one LDS round trip
-        _Float16 x[7];
-#pragma unroll
-        for (int sl = 0; sl < 7; sl++) x[sl] = le(xrow, f[sl]);
-#pragma unroll
-        for (int sl = 0; sl < 7; sl++) g |= (x[sl] <= thr[sl] ? 0u : 1u) << sl;
-    } else {
-#pragma unroll
-        for (int sl = 0; sl < 7; sl++) g |= (le(xrow, f[sl], thr[sl]) ? 0u : 1u) << sl;
-    }
-    const uint32_t g4 = __builtin_amdgcn_perm(g, g, 0u);  // byte 0 of g copied into every byte
-    const uint32_t z_lo = zero_bytes((g4 ^ val_lo) & care_lo), z_hi = zero_bytes((g4 ^ val_hi) & care_hi);
-    // a verified block's used exits partition the outcomes: exactly one byte
-    // is zero (the top bit keeps e <= 7 for any bytes); both outcomes of the
-    // exit are formed and selected, without a branch
-    const uint64_t z = ((uint64_t)(z_hi | 0x80000000u) << 32) | z_lo;
-    const uint32_t e = (uint32_t)__builtin_ctzll(z) >> 3;
-    const uint64_t targets = ((uint64_t)r[1] << 32) | r[0];
-    const uint32_t t = (uint32_t)(targets >> __umul24(e, 6u)) & 63u;
-    const int32_t child = (int32_t)(child_base + min(t & 7u, n_child - 1u));
-    const int32_t leaf = ~(int32_t)(t & 31u);
-    const int32_t m = -(int32_t)(t >> 5);  // all ones when the exit leads to a child block
-    return (child & m) | (leaf & ~m);
-}
-
 // BLOCKED layout walk.  Every reference is a block of the bin (or a class).
 // A block is fetched whole and walked for up to three levels from registers:
 // slot 0, then slot 1 or 2, then one of slots 3..6, ending in a class or an
@@ -787,14 +785,11 @@ __device__ __forceinline__ int32_t cluster_step(const uint4 (&q)[4], int32_t xro
 // features in LDS all seven split tests are read in one LDS round trip and
 // the path is resolved from a mask of sides by selects (no divergence inside
 // a block).
-// FMT: 0 BLOCKED 48-byte blocks, 1 BLOCKED 64-byte blocks, 2 CLUSTERED
-// 64-byte blocks, 3 CLUSTERED 48-byte blocks, 4 CLUSTERED 48-byte blocks
-// over an fp16 tile (features in LDS only).
-template <int K, int FMODE, int FMT>
-__device__ void run_tile_blocked(const JobDesc& j, int nt, int tile, unsigned char* smem) {
-    constexpr bool B48 = FMT == 0 || FMT >= 3;
-    constexpr bool X16 = FMT == 4;
-    static_assert(!X16 || FMODE != 0, "an fp16 tile lives in LDS (x16 is set only with feat_lds)");
+// Only forests without a walk form (classes or features beyond its fields)
+// come here: run_tile_walk below is the faster walk of the same blocks.
+// B48: 48-byte blocks, else 64-byte ones.
+template <int K, int FMODE, bool B48>
+__device__ __forceinline__ void run_tile_blocked(const JobDesc& j, int nt, int tile, unsigned char* smem) {
     const bool feat_lds = FMODE == 2 ? (j.feat_lds != 0) : (FMODE == 1);
     const int4* ttab = reinterpret_cast<const int4*>(smem + j.off_ttab);
     const int32_t* fmap_l = reinterpret_cast<const int32_t*>(smem + j.off_fmap);
@@ -809,8 +804,7 @@ __device__ void run_tile_blocked(const JobDesc& j, int nt, int tile, unsigned ch
     const uint32_t sh_l = (uint32_t)fb, sh_r = (uint32_t)(fb + cw);  // where the left / right codes start
 
     const int64_t row0 = (int64_t)tile * j.R;
-    const int rows_here = (int)min<int64_t>(j.R, j.n_rows - row0);
-    stage_tile<X16>(j, xs, vl, pool, row0, rows_here, feat_lds);
+    const int rows_here = tile_rows(j, row0);
 
     const int U = rows_here * nt;
     const uint32_t rmagic = 0xFFFFFFFFu / (uint32_t)rows_here;
@@ -820,13 +814,6 @@ __device__ void run_tile_blocked(const JobDesc& j, int nt, int tile, unsigned ch
     auto le = [&](int32_t xrow, uint32_t f, float thr) {
         const float x = feat_lds ? lds_ptr<float>((uint32_t)xrow)[f] : j.X[(row0 + xrow) * j.ld + fmap_l[f]];
         return x <= thr;
-    };
-    // the same over an fp16 tile (feature-major, feature stride Fcp): exact
-    // for thresholds exact in fp16, since the tile holds each x rounded
-    // toward +infinity
-    const uint32_t fstride = 2u * (uint32_t)j.Fcp;
-    auto le16 = [&](int32_t xrow, uint32_t f) -> _Float16 {
-        return *lds_ptr<_Float16>((uint32_t)xrow + __umul24(f, fstride));
     };
     const uint32_t xs_addr = lds_addr(xs), blocks_addr = lds_addr(smem + j.off_top);
     // the block an exit leaves to: rank from the code (48-byte form) or the table
@@ -844,9 +831,7 @@ __device__ void run_tile_blocked(const JobDesc& j, int nt, int tile, unsigned ch
         ref[k] = kDone; xrow[k] = 0; vrow[k] = 0; ns[k] = 0; la[k] = 0; bp[k] = nullptr;
     }
     auto take = [&](int k, int r, int4 e) -> int32_t {
-        xrow[k] = !feat_lds ? r
-                  : X16     ? (int32_t)(xs_addr + 2u * (uint32_t)r)
-                            : (int32_t)(xs_addr + 4u * __umul24((uint32_t)r, (uint32_t)j.Fcp));
+        xrow[k] = feat_lds ? (int32_t)(xs_addr + 4u * __umul24((uint32_t)r, (uint32_t)j.Fcp)) : r;
         vrow[k] = (int32_t)__umul24((uint32_t)r, (uint32_t)j.C);
         bp[k] = (const global_u32x4*)(words + e.y);
         la[k] = blocks_addr + 16u * (uint32_t)e.z;
@@ -875,11 +860,7 @@ __device__ void run_tile_blocked(const JobDesc& j, int nt, int tile, unsigned ch
         for (int k = 0; k < K; k++) {
             if (ref[k] < 0) continue;
             int32_t nr;
-            if constexpr (X16) {
-                nr = cluster_step<true, true>(q[k], xrow[k], le16);
-            } else if constexpr (FMT >= 2) {
-                nr = cluster_step<FMT == 3, false>(q[k], xrow[k], le);
-            } else if (const BlockView b = view_block<B48>(q[k]); feat_lds) {
+            if (const BlockView b = view_block<B48>(q[k]); feat_lds) {
                 // all seven split tests (absent slots are zero words: feature
                 // 0, harmless) packed into a mask of sides, bit s set = slot s
                 // goes right; the path reads the mask, so the seven LDS reads
@@ -934,46 +915,528 @@ __device__ void run_tile_blocked(const JobDesc& j, int nt, int tile, unsigned ch
     write_tile(j, vl, row0, rows_here);
 }
 
+// ---------------------------------------------------------------------------
+// Walk form (fp_internal.h): conversion at upload, and the walk over it
+// ---------------------------------------------------------------------------
+// Blocks [lo, hi) of every bin, one thread each (blockIdx.y strides over
+// bins): reads the host form and writes the walk form, block k at k times its
+// smaller size from the bin's start.  The caller picks [lo, hi) so that what
+// it writes was read by this workgroup before the barrier or by an earlier
+// launch.
+__global__ __launch_bounds__(256) void walk_form_kernel(const BinEntry* __restrict__ bins, int32_t n_bins, uint32_t* nodes,
+                                                        int32_t layout, int32_t form, int32_t block_bytes, int32_t fbits,
+                                                        int32_t cbits, int64_t lo, int64_t hi) {
+    const int bd = block_bytes / 4;
+    const fp::WalkShape ws = fp::walk_shape(form);
+    const int64_t k = lo + (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    for (int32_t b = blockIdx.y; b < n_bins; b += gridDim.y) {
+        const int64_t unit0 = bins[b].node_base / 2;  // the bin's first 16-byte unit
+        const bool live = k < hi && k < bins[b].deep_len;
+        uint32_t* const bin = nodes + unit0 * 4;
+        uint32_t w[16];
+        for (int i = 0; i < 16; i++) w[i] = live && i < bd ? bin[k * bd + i] : 0u;
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        __syncthreads();  // every block of the workgroup has been read before any is written
+        if (!live) continue;
+        uint32_t thr0[7], feat0[7], kill[7], to[8], child;
+        int n_exits = 0;
+        for (int s = 0; s < 7; s++) kill[s] = 0;
+        for (int e = 0; e < 8; e++) to[e] = ws.leaf;
+        if (layout == FP_LAYOUT_CLUSTERED) {
+            const bool c48 = block_bytes == 48;
+            const int cv = c48 ? 4 : 7, rest = c48 ? 8 : 11;  // dwords of care/val bytes, of rest
+            auto bits = [&](int pos, int width) -> uint32_t {  // rest bits; 48-byte form: bits from 128 in dword 3's high half
+                const int i = pos / 32;
+                const uint32_t l = w[rest + i];
+                const uint32_t h = i + 1 < (c48 ? 4 : 5) ? w[rest + i + 1] : c48 ? w[3] >> 16 : 0u;
+                return (uint32_t)((((uint64_t)h << 32) | l) >> (pos % 32)) & ((1u << width) - 1u);
+            };
+            uint32_t care[8], val[8];
+            for (int e = 0; e < 8; e++) {
+                care[e] = (w[cv + e / 4] >> (8 * (e % 4))) & 255u;
+                val[e] = (w[cv + 2 + e / 4] >> (8 * (e % 4))) & 255u;
+                n_exits += !(care[e] & 0x80u);
+            }
+            for (int s = 0; s < 7; s++) {
+                if (c48) {
+                    thr0[s] = (w[s / 2] >> (16 * (s % 2))) & 0xFFFFu;
+                    feat0[s] = bits(s == 0 ? 48 : s <= 3 ? 64 + 9 * (s - 1) : 96 + 9 * (s - 4), fp::kCluster48FeatBits);
+                } else {
+                    thr0[s] = w[s];
+                    feat0[s] = bits(48 + fp::kClusterFeatBits * s, fp::kClusterFeatBits);
+                }
+            }
+            static_assert(fp::kC48FeatPos[0] == 48 && fp::kC48FeatPos[1] == 64 && fp::kC48FeatPos[3] == 82 &&
+                              fp::kC48FeatPos[4] == 96 && fp::kC48FeatPos[6] == 114,
+                          "feature positions of the 48-byte block");
+            child = c48 ? bits(fp::kC48BasePos, fp::kC48BaseBits) : bits(132, 24);
+            // two exits part at the one slot they both test with different
+            // outcomes: the exit that goes left there lies left
+            for (int e = 0; e < 8; e++) {
+                if (care[e] & 0x80u) continue;  // unused
+                int at = 0;
+                for (int o = 0; o < 8; o++)
+                    if (!(care[o] & 0x80u)) at += (val[e] & care[e] & care[o] & (val[e] ^ val[o])) != 0;  // o lies left of e
+                const uint32_t t = bits(6 * e, 6), target = (t & 32u) ? (t & 7u) : ws.leaf | (t & 31u);
+                for (int x = 0; x < 8; x++) to[x] = x == at ? target : to[x];
+                for (int s = 0; s < 7; s++)
+                    if ((care[e] >> s & 1u) && !(val[e] >> s & 1u)) kill[s] |= 1u << at;
+            }
+        } else {
+            const bool b48 = block_bytes == 48;
+            const int cw = 1 + (b48 ? max(cbits, 3) : cbits);
+            const uint32_t cmask = (1u << cw) - 1u, fmask = (1u << fbits) - 1u;
+            uint32_t code[14];
+            for (int s = 0; s < 7; s++) {
+                uint32_t word;
+                if (b48) {
+                    const int o = fp::kBlock48WordBits * s;
+                    const uint64_t two = ((uint64_t)(o / 32 + 1 < 5 ? w[o / 32 + 1] : 0u) << 32) | w[o / 32];
+                    word = (uint32_t)(two >> (o % 32)) & ((1u << fp::kBlock48WordBits) - 1u);
+                    thr0[s] = w[5 + s];
+                } else {
+                    word = w[3 + 2 * s];
+                    thr0[s] = w[2 + 2 * s];
+                }
+                feat0[s] = word & fmask;
+                code[2 * s] = (word >> fbits) & cmask;
+                code[2 * s + 1] = (word >> (fbits + cw)) & cmask;
+            }
+            child = b48 ? w[4] >> 8 : w[0];
+            for (int e = 0; e < 8; e++) {
+                // the first class on the path to bottom exit e, else its child block
+                const uint32_t c0 = code[e / 4], c1 = code[2 * (1 + e / 4) + (e / 2) % 2], c2 = code[6 + e];
+                const uint32_t c = (c0 & 1u) ? c0 : (c1 & 1u) ? c1 : c2;
+                to[e] = (c & 1u) ? ws.leaf | (c >> 1) : b48 ? c2 >> 1 : (w[1] >> (4 * e)) & 7u;
+            }
+            kill[0] = 15; kill[1] = 3; kill[2] = 48; kill[3] = 1; kill[4] = 4; kill[5] = 16; kill[6] = 64;
+            n_exits = 8;
+        }
+        // slots in order (the place of a slot is the last exit of its left
+        // subtree), exits beyond the block's own repeating its last one
+        uint32_t thr[7], feat[7], mask[7];
+        for (int i = 0; i < 7; i++) {
+            thr[i] = feat[i] = mask[i] = 0;
+            for (int s = 0; s < 7; s++)
+                if (kill[s] && 31 - __builtin_clz(kill[s]) == i) { thr[i] = thr0[s]; feat[i] = feat0[s]; mask[i] = kill[s]; }
+        }
+        if (form == fp::kWalk48b)  // in the tree's own order, its masks are constants
+            for (int s = 0; s < 7; s++) { thr[s] = thr0[s]; feat[s] = feat0[s]; }
+        for (int e = 1; e < 8; e++) to[e] = e < n_exits ? to[e] : to[e - 1];
+        uint64_t targets = 0;
+        for (int e = 0; e < 8; e++) targets |= (uint64_t)to[e] << (ws.tbits * e);
+        uint32_t below = 0;  // the stored mask bits: slot i's i bits below bit i, from bit i (i - 1) / 2
+        for (int i = 1; i < 7; i++) below |= (mask[i] & ((1u << i) - 1u)) << (i * (i - 1) / 2);
+        const uint32_t base = (uint32_t)(fp::kGlobalRef + unit0 / (ws.unit / 16) + (int64_t)child * (ws.bytes / ws.unit));
+        const uint32_t t_lo = (uint32_t)targets, t_hi = (uint32_t)(targets >> 32);
+        const uint32_t m_lo = mask[0] | mask[1] << 8 | mask[2] << 16 | mask[3] << 24, m_hi = mask[4] | mask[5] << 8 | mask[6] << 16;
+        const uint32_t f10a = feat[0] | feat[1] << 10 | feat[2] << 20, f10b = feat[3] | feat[4] << 10 | feat[5] << 20;
+        uint32_t* d = bin + k * (ws.bytes / 4);
+        if (form == fp::kWalk64) {
+            for (int s = 0; s < 7; s++) d[s] = thr[s];
+            d[7] = m_lo;
+            d[8] = m_hi;
+            for (int s = 0; s < 3; s++) d[9 + s] = feat[2 * s] | feat[2 * s + 1] << 16;
+            d[12] = feat[6];
+            d[13] = t_lo;
+            d[14] = t_hi;
+            d[15] = base;
+        } else if (form == fp::kWalk48h) {
+            for (int s = 0; s < 3; s++) d[s] = thr[2 * s] | thr[2 * s + 1] << 16;
+            d[3] = thr[6] | feat[6] << 16;
+            for (int s = 0; s < 3; s++) d[4 + s] = feat[2 * s] | feat[2 * s + 1] << 16;
+            d[7] = m_lo;
+            d[8] = base;
+            d[9] = t_lo;
+            d[10] = t_hi;
+            d[11] = m_hi;
+        } else if (form == fp::kWalk32h) {
+            // mask 6 is a run that ends in bit 6: its start
+            const uint32_t start6 = mask[6] ? (uint32_t)__builtin_ctz(mask[6]) : 6u;
+            for (int s = 0; s < 3; s++) d[s] = thr[2 * s] | thr[2 * s + 1] << 16;
+            d[3] = thr[6] | (below & 0x7FFFu) << 16;
+            d[4] = feat[0] | feat[1] << 9 | feat[2] << 18 | (feat[6] & 31u) << 27;
+            d[5] = feat[3] | feat[4] << 9 | feat[5] << 18 | (feat[6] >> 5) << 27;
+            d[6] = t_lo;
+            d[7] = t_hi | base << 8 | start6 << 28;
+        } else {
+            for (int s = 0; s < 7; s++) d[s] = thr[s];
+            d[7] = f10a;
+            d[8] = f10b;
+            if (form == fp::kWalk48f) {
+                d[9] = feat[6] | below << 10;
+                d[10] = t_lo;
+                d[11] = base;
+            } else {
+                d[9] = base;
+                d[10] = t_lo;
+                d[11] = t_hi | feat[6] << 16;
+            }
+        }
+    }
+}
+
+// a + half HI of w times m (16 bits each): one instruction.
+template <int HI>
+__device__ __forceinline__ uint32_t mad_half(uint32_t w, uint32_t m, uint32_t a) {
+    uint32_t r;
+    if constexpr (HI) asm("v_mad_u32_u16 %0, %1, %2, %3 op_sel:[1,0,0,0]" : "=v"(r) : "v"(w), "s"(m), "v"(a));
+    else asm("v_mad_u32_u16 %0, %1, %2, %3" : "=v"(r) : "v"(w), "s"(m), "v"(a));
+    return r;
+}
+
+// Exits killed by a block's seven tests: per slot one compare that leaves
+// only the lanes going right (!(x <= t): NaN goes right) active, and one OR
+// of the slot's kill byte under that mask.  exec is the caller's on exit.
+#define FP_KILL(CMP, M) CMP "\n\t" M "\n\ts_mov_b64 exec, %[sv]\n\t"
+#define FP_OR_BYTE(W, B) "v_or_b32_sdwa %[k], %[k], %[" W "] dst_sel:DWORD dst_unused:UNUSED_PAD src0_sel:DWORD src1_sel:BYTE_" B
+__device__ __forceinline__ uint32_t killed_f32(const float (&x)[7], const float (&t)[7], uint32_t lo, uint32_t hi) {
+    uint32_t k = 0;
+    uint64_t sv;
+    asm volatile("s_mov_b64 %[sv], exec\n\t"
+                 FP_KILL("v_cmpx_nle_f32_e32 vcc, %[x0], %[t0]", FP_OR_BYTE("lo", "0"))
+                 FP_KILL("v_cmpx_nle_f32_e32 vcc, %[x1], %[t1]", FP_OR_BYTE("lo", "1"))
+                 FP_KILL("v_cmpx_nle_f32_e32 vcc, %[x2], %[t2]", FP_OR_BYTE("lo", "2"))
+                 FP_KILL("v_cmpx_nle_f32_e32 vcc, %[x3], %[t3]", FP_OR_BYTE("lo", "3"))
+                 FP_KILL("v_cmpx_nle_f32_e32 vcc, %[x4], %[t4]", FP_OR_BYTE("hi", "0"))
+                 FP_KILL("v_cmpx_nle_f32_e32 vcc, %[x5], %[t5]", FP_OR_BYTE("hi", "1"))
+                 FP_KILL("v_cmpx_nle_f32_e32 vcc, %[x6], %[t6]", FP_OR_BYTE("hi", "2"))
+                 : [k] "+v"(k), [sv] "=&s"(sv)
+                 : [x0] "v"(x[0]), [x1] "v"(x[1]), [x2] "v"(x[2]), [x3] "v"(x[3]), [x4] "v"(x[4]), [x5] "v"(x[5]),
+                   [x6] "v"(x[6]), [t0] "v"(t[0]), [t1] "v"(t[1]), [t2] "v"(t[2]), [t3] "v"(t[3]), [t4] "v"(t[4]),
+                   [t5] "v"(t[5]), [t6] "v"(t[6]), [lo] "v"(lo), [hi] "v"(hi)
+                 : "vcc");
+    return k;
+}
+// fp16 features (low halves of x) against the fp16 thresholds t01 .. t6 (two to a word, t6 low).
+__device__ __forceinline__ uint32_t killed_f16(const uint32_t (&x)[7], uint32_t t01, uint32_t t23, uint32_t t45,
+                                               uint32_t t6, uint32_t lo, uint32_t hi) {
+    uint32_t k = 0;
+    uint64_t sv;
+#define FP_NLE_HI(X, T) "v_cmpx_nle_f16_sdwa vcc, %[" X "], %[" T "] src0_sel:DWORD src1_sel:WORD_1"
+    asm volatile("s_mov_b64 %[sv], exec\n\t"
+                 FP_KILL("v_cmpx_nle_f16_e32 vcc, %[x0], %[t01]", FP_OR_BYTE("lo", "0"))
+                 FP_KILL(FP_NLE_HI("x1", "t01"), FP_OR_BYTE("lo", "1"))
+                 FP_KILL("v_cmpx_nle_f16_e32 vcc, %[x2], %[t23]", FP_OR_BYTE("lo", "2"))
+                 FP_KILL(FP_NLE_HI("x3", "t23"), FP_OR_BYTE("lo", "3"))
+                 FP_KILL("v_cmpx_nle_f16_e32 vcc, %[x4], %[t45]", FP_OR_BYTE("hi", "0"))
+                 FP_KILL(FP_NLE_HI("x5", "t45"), FP_OR_BYTE("hi", "1"))
+                 FP_KILL("v_cmpx_nle_f16_e32 vcc, %[x6], %[t6]", FP_OR_BYTE("hi", "2"))
+                 : [k] "+v"(k), [sv] "=&s"(sv)
+                 : [x0] "v"(x[0]), [x1] "v"(x[1]), [x2] "v"(x[2]), [x3] "v"(x[3]), [x4] "v"(x[4]), [x5] "v"(x[5]),
+                   [x6] "v"(x[6]), [t01] "v"(t01), [t23] "v"(t23), [t45] "v"(t45), [t6] "v"(t6), [lo] "v"(lo),
+                   [hi] "v"(hi)
+                 : "vcc");
+    return k;
+}
+// Masks in registers.  m[i]: slot i's bits below bit i; bit i itself is a constant.
+#define FP_OR_MASK(I, C) "v_or3_b32 %[k], %[k], %[m" I "], " C
+__device__ __forceinline__ uint32_t killed_f32(const float (&x)[7], const float (&t)[7], const uint32_t (&m)[7]) {
+    uint32_t k = 0;
+    uint64_t sv;
+    asm volatile("s_mov_b64 %[sv], exec\n\t"
+                 FP_KILL("v_cmpx_nle_f32_e32 vcc, %[x0], %[t0]", "v_or_b32_e32 %[k], 1, %[k]")
+                 FP_KILL("v_cmpx_nle_f32_e32 vcc, %[x1], %[t1]", FP_OR_MASK("1", "2"))
+                 FP_KILL("v_cmpx_nle_f32_e32 vcc, %[x2], %[t2]", FP_OR_MASK("2", "4"))
+                 FP_KILL("v_cmpx_nle_f32_e32 vcc, %[x3], %[t3]", FP_OR_MASK("3", "8"))
+                 FP_KILL("v_cmpx_nle_f32_e32 vcc, %[x4], %[t4]", FP_OR_MASK("4", "16"))
+                 FP_KILL("v_cmpx_nle_f32_e32 vcc, %[x5], %[t5]", FP_OR_MASK("5", "32"))
+                 FP_KILL("v_cmpx_nle_f32_e32 vcc, %[x6], %[t6]", FP_OR_MASK("6", "64"))
+                 : [k] "+v"(k), [sv] "=&s"(sv)
+                 : [x0] "v"(x[0]), [x1] "v"(x[1]), [x2] "v"(x[2]), [x3] "v"(x[3]), [x4] "v"(x[4]), [x5] "v"(x[5]),
+                   [x6] "v"(x[6]), [t0] "v"(t[0]), [t1] "v"(t[1]), [t2] "v"(t[2]), [t3] "v"(t[3]), [t4] "v"(t[4]),
+                   [t5] "v"(t[5]), [t6] "v"(t[6]), [m1] "v"(m[1]), [m2] "v"(m[2]), [m3] "v"(m[3]), [m4] "v"(m[4]),
+                   [m5] "v"(m[5]), [m6] "v"(m[6])
+                 : "vcc");
+    return k;
+}
+__device__ __forceinline__ uint32_t killed_f16(const uint32_t (&x)[7], uint32_t t01, uint32_t t23, uint32_t t45, uint32_t t6,
+                                               const uint32_t (&m)[7]) {
+    uint32_t k = 0;
+    uint64_t sv;
+    asm volatile("s_mov_b64 %[sv], exec\n\t"
+                 FP_KILL("v_cmpx_nle_f16_e32 vcc, %[x0], %[t01]", "v_or_b32_e32 %[k], 1, %[k]")
+                 FP_KILL(FP_NLE_HI("x1", "t01"), FP_OR_MASK("1", "2"))
+                 FP_KILL("v_cmpx_nle_f16_e32 vcc, %[x2], %[t23]", FP_OR_MASK("2", "4"))
+                 FP_KILL(FP_NLE_HI("x3", "t23"), FP_OR_MASK("3", "8"))
+                 FP_KILL("v_cmpx_nle_f16_e32 vcc, %[x4], %[t45]", FP_OR_MASK("4", "16"))
+                 FP_KILL(FP_NLE_HI("x5", "t45"), FP_OR_MASK("5", "32"))
+                 FP_KILL("v_cmpx_nle_f16_e32 vcc, %[x6], %[t6]", FP_OR_MASK("6", "64"))
+                 : [k] "+v"(k), [sv] "=&s"(sv)
+                 : [x0] "v"(x[0]), [x1] "v"(x[1]), [x2] "v"(x[2]), [x3] "v"(x[3]), [x4] "v"(x[4]), [x5] "v"(x[5]),
+                   [x6] "v"(x[6]), [t01] "v"(t01), [t23] "v"(t23), [t45] "v"(t45), [t6] "v"(t6), [m1] "v"(m[1]),
+                   [m2] "v"(m[2]), [m3] "v"(m[3]), [m4] "v"(m[4]), [m5] "v"(m[5]), [m6] "v"(m[6])
+                 : "vcc");
+    return k;
+}
+#undef FP_OR_MASK
+#undef FP_NLE_HI
+// A complete three-level subtree: the kill masks are constants.
+__device__ __forceinline__ uint32_t killed_full(const float (&x)[7], const float (&t)[7]) {
+    uint32_t k = 0;
+    uint64_t sv;
+#define FP_OR_CONST(C) "v_or_b32_e32 %[k], " C ", %[k]"
+    asm volatile("s_mov_b64 %[sv], exec\n\t"
+                 FP_KILL("v_cmpx_nle_f32_e32 vcc, %[x0], %[t0]", FP_OR_CONST("15"))
+                 FP_KILL("v_cmpx_nle_f32_e32 vcc, %[x1], %[t1]", FP_OR_CONST("3"))
+                 FP_KILL("v_cmpx_nle_f32_e32 vcc, %[x2], %[t2]", FP_OR_CONST("48"))
+                 FP_KILL("v_cmpx_nle_f32_e32 vcc, %[x3], %[t3]", FP_OR_CONST("1"))
+                 FP_KILL("v_cmpx_nle_f32_e32 vcc, %[x4], %[t4]", FP_OR_CONST("4"))
+                 FP_KILL("v_cmpx_nle_f32_e32 vcc, %[x5], %[t5]", FP_OR_CONST("16"))
+                 FP_KILL("v_cmpx_nle_f32_e32 vcc, %[x6], %[t6]", FP_OR_CONST("64"))
+                 : [k] "+v"(k), [sv] "=&s"(sv)
+                 : [x0] "v"(x[0]), [x1] "v"(x[1]), [x2] "v"(x[2]), [x3] "v"(x[3]), [x4] "v"(x[4]), [x5] "v"(x[5]),
+                   [x6] "v"(x[6]), [t0] "v"(t[0]), [t1] "v"(t[1]), [t2] "v"(t[2]), [t3] "v"(t[3]), [t4] "v"(t[4]),
+                   [t5] "v"(t[5]), [t6] "v"(t[6])
+                 : "vcc");
+#undef FP_OR_CONST
+    return k;
+}
+#undef FP_OR_BYTE
+#undef FP_KILL
+
+// Low / high fp16 half of a word widened to fp32 (exact).
+__device__ __forceinline__ float half_lo(uint32_t v) {
+    return (float)__builtin_bit_cast(_Float16, (unsigned short)(v & 0xFFFFu));
+}
+__device__ __forceinline__ float half_hi(uint32_t v) {
+    return (float)__builtin_bit_cast(_Float16, (unsigned short)(v >> 16));
+}
+
+// One step: decodes the block in q and returns the next reference, or the
+// target of a leaf with `leaf` set.
+template <int FMODE, int FORM, bool X16>
+__device__ __forceinline__ int32_t walk_step(const JobDesc& j, const uint4 (&q)[4], uint32_t xrow, uint32_t es, int64_t row0,
+                                             const int32_t* fmap_l, bool& leaf) {
+    constexpr fp::WalkShape ws = fp::walk_shape(FORM);
+    constexpr bool F16 = FORM == fp::kWalk48h || FORM == fp::kWalk32h;
+    constexpr bool BELOW = FORM == fp::kWalk48f || FORM == fp::kWalk32h;  // masks stored as the bits below each slot's
+    // LDS address (or number) of slot s's feature
+    uint32_t at[7];
+    const uint32_t m = FMODE == 1 ? es : 1u, a0 = FMODE == 1 ? xrow : 0u;
+    if constexpr (FORM == fp::kWalk48b || FORM == fp::kWalk48f || FORM == fp::kWalk32h) {
+        constexpr int fb = FORM == fp::kWalk32h ? 9 : 10;
+        const uint32_t fw[2] = {FORM == fp::kWalk32h ? q[1].x : q[1].w, FORM == fp::kWalk32h ? q[1].y : q[2].x};
+#pragma unroll
+        for (int s = 0; s < 6; s++) at[s] = a0 + __umul24((fw[s / 3] >> (fb * (s % 3))) & ((1u << fb) - 1u), m);
+        if constexpr (FORM == fp::kWalk48b) at[6] = mad_half<1>(q[2].w, m, a0);
+        else if constexpr (FORM == fp::kWalk48f) at[6] = a0 + __umul24(q[2].y & 1023u, m);
+        else at[6] = a0 + __umul24(__builtin_amdgcn_alignbit(q[1].y >> 27, q[1].x, 27), m);
+    } else {
+        const uint32_t fw[3] = {FORM == fp::kWalk64 ? q[2].y : q[1].x, FORM == fp::kWalk64 ? q[2].z : q[1].y,
+                                FORM == fp::kWalk64 ? q[2].w : q[1].z};
+#pragma unroll
+        for (int s = 0; s < 3; s++) {
+            at[2 * s] = mad_half<0>(fw[s], m, a0);
+            at[2 * s + 1] = mad_half<1>(fw[s], m, a0);
+        }
+        at[6] = FORM == fp::kWalk48h ? mad_half<1>(q[0].w, m, a0) : mad_half<0>(q[3].x, m, a0);
+    }
+    uint32_t mask[7] = {0, 0, 0, 0, 0, 0, 0};
+    if constexpr (BELOW) {
+        const uint32_t w = FORM == fp::kWalk48f ? q[2].y : q[0].w;
+        constexpr int o = FORM == fp::kWalk48f ? 10 : 16;
+#pragma unroll
+        for (int i = 1; i < 7; i++) mask[i] = (w >> (o + i * (i - 1) / 2)) & ((1u << i) - 1u);
+        if constexpr (FORM == fp::kWalk32h) mask[6] = (0x7Fu << (q[1].w >> 28)) & 0x7Fu;
+    }
+    uint32_t killed;
+    if constexpr (X16) {
+        uint32_t x[7];
+#pragma unroll
+        for (int s = 0; s < 7; s++) x[s] = *lds_ptr<uint16_t>(at[s]);
+        if constexpr (BELOW) killed = killed_f16(x, q[0].x, q[0].y, q[0].z, q[0].w, mask);
+        else killed = killed_f16(x, q[0].x, q[0].y, q[0].z, q[0].w, q[1].w, q[2].w);
+    } else {
+        float x[7], t[7];
+#pragma unroll
+        for (int s = 0; s < 7; s++)
+            x[s] = FMODE == 1 ? *lds_ptr<float>(at[s]) : j.X[(row0 + (int64_t)xrow) * j.ld + fmap_l[at[s]]];
+        if constexpr (F16) {
+            t[0] = half_lo(q[0].x); t[1] = half_hi(q[0].x); t[2] = half_lo(q[0].y); t[3] = half_hi(q[0].y);
+            t[4] = half_lo(q[0].z); t[5] = half_hi(q[0].z); t[6] = half_lo(q[0].w);
+        } else {
+            t[0] = __uint_as_float(q[0].x); t[1] = __uint_as_float(q[0].y); t[2] = __uint_as_float(q[0].z);
+            t[3] = __uint_as_float(q[0].w); t[4] = __uint_as_float(q[1].x); t[5] = __uint_as_float(q[1].y);
+            t[6] = __uint_as_float(q[1].z);
+        }
+        if constexpr (FORM == fp::kWalk48b) killed = killed_full(x, t);
+        else if constexpr (BELOW) killed = killed_f32(x, t, mask);
+        else killed = killed_f32(x, t, q[1].w, FORM == fp::kWalk64 ? q[2].x : q[2].w);
+    }
+    const uint32_t e = (uint32_t)__builtin_ctz(~killed);  // the lowest exit alive, 0..7
+    uint32_t t, base;
+    if constexpr (FORM == fp::kWalk64) {
+        t = __builtin_amdgcn_perm(q[3].z, q[3].y, e | 0x0C0C0C00u);
+        base = q[3].w;
+    } else if constexpr (FORM == fp::kWalk48h) {
+        t = __builtin_amdgcn_perm(q[2].z, q[2].y, e | 0x0C0C0C00u);
+        base = q[2].x;
+    } else if constexpr (FORM == fp::kWalk48f) {
+        t = (q[2].z >> (4u * e)) & 15u;
+        base = q[2].w;
+    } else if constexpr (FORM == fp::kWalk48b) {
+        t = (uint32_t)((((uint64_t)q[2].w << 32) | q[2].z) >> (6u * e)) & 63u;
+        base = q[2].y;
+    } else {
+        t = (uint32_t)((((uint64_t)q[1].w << 32) | q[1].z) >> (5u * e)) & 31u;
+        base = (q[1].w >> 8) & 0xFFFFFu;
+    }
+    leaf = (t & ws.leaf) != 0;
+    return leaf ? (int32_t)t : (int32_t)(base + __umul24(t, (uint32_t)(ws.bytes / ws.unit)));
+}
+
+// The walk over blocks in their walk form: one walk per lane, a block a step
+// (two per lane were no faster on the large tabular forest, 7.00 against
+// 7.03 ms, and slower on the image one, 2.27 against 1.67 ms).
+// X16: the tile holds fp16 features (forms with fp16 thresholds).  A walk's state is its
+// reference (LDS or memory, see fp_internal.h), the LDS address of its row's
+// features (or its row, when features stay in memory) and of its votes.
+// Bound by 16-byte pieces a lane loads (0.74 cycles of the CU's vector memory
+// path each) together with LDS (seven feature reads a step, 8 cycles a
+// wavefront at random banks) and instruction issue; the working set hardly
+// matters (210-260 G blocks/s from 2 MB to 300 MB of forest).  Against host
+// blocks with care/value exit patterns (80 VALU instructions a step, four or
+// three pieces): 1M image rows x 128 trees 2.03 -> 1.64 ms, 2M tabular rows x
+// 160 trees 8.30 -> 7.04 ms, 4,096 rows x 1,024 trees 231 -> 191 us.
+template <int FMODE, int FORM, bool X16>
+__device__ __forceinline__ void run_tile_walk(const JobDesc& j, int nt, int tile, unsigned char* smem) {
+    static_assert(!X16 || (FMODE == 1 && (FORM == fp::kWalk48h || FORM == fp::kWalk32h)),
+                  "fp16 tiles live in LDS and need fp16 thresholds");
+    constexpr fp::WalkShape ws = fp::walk_shape(FORM);
+    constexpr int bw = ws.bytes / 16;
+    const int32_t* ttab = reinterpret_cast<const int32_t*>(smem + j.off_ttab);
+    const int32_t* fmap_l = reinterpret_cast<const int32_t*>(smem + j.off_fmap);
+    float* xs = reinterpret_cast<float*>(smem + j.off_xs);
+    int32_t* vl = reinterpret_cast<int32_t*>(smem + j.off_votes);
+    int32_t* pool = reinterpret_cast<int32_t*>(smem + j.off_pool);
+    const int lane = lane_id();
+
+    const int64_t row0 = (int64_t)tile * j.R;
+    const int rows_here = tile_rows(j, row0);
+
+    const int U = rows_here * nt;
+    const uint32_t rmagic = 0xFFFFFFFFu / (uint32_t)rows_here;
+    const uint32_t es = X16 ? 2u * (uint32_t)j.Fcp : 4u;  // bytes from one feature of a row to the next
+    const uint32_t rs = X16 ? 2u : 4u * (uint32_t)j.Fcp;  // and from one row to the next
+    const uint32_t xs_addr = lds_addr(xs), pool_addr = lds_addr(pool);
+    const uint32_t votes_addr = lds_addr(vl) - 4u * ws.leaf;  // a target with its leaf bit indexes from here
+    const global_u32x4* gbase = (const global_u32x4*)j.nodes - fp::kGlobalRef * (ws.unit / 16);
+    int32_t ref = kDone;
+    uint32_t xrow = 0, vrow = 0;
+    bool drained = false;
+    while (true) {
+        uint64_t idle = __ballot(ref < 0);
+        int cnt = (int)__popcll(idle);
+        while (cnt >= j.refill_min && !drained) {
+            int base = 0;
+            if (lane == 0)
+                asm volatile("ds_add_rtn_u32 %0, %1, %2\n\ts_waitcnt lgkmcnt(0)" : "=&v"(base) : "v"(pool_addr), "v"(cnt) : "memory");
+            base = __builtin_amdgcn_readfirstlane(base);
+            drained = base + cnt >= U;
+            if (ref < 0) {
+                const uint32_t u = (uint32_t)(base + bits_below(idle));
+                if (u < (uint32_t)U) {
+                    uint32_t r;
+                    const uint32_t t = div_rows(u, (uint32_t)rows_here, rmagic, r);
+                    ref = ttab[t];
+                    xrow = FMODE == 1 ? xs_addr + __umul24(r, rs) : r;
+                    vrow = votes_addr + 4u * __umul24(r, (uint32_t)j.C);
+                    if (ref < 0) {  // the root is a leaf
+                        atomicAdd(&vl[__umul24(r, (uint32_t)j.C) - ref - 1], 1);
+                        ref = kDone;
+                    }
+                }
+            }
+            idle = __ballot(ref < 0);
+            cnt = (int)__popcll(idle);
+        }
+        if (cnt == 64) break;  // a wavefront with nothing live has drained the pool
+        // LDS blocks first: the loads from memory into the same registers
+        // then wait for LDS only, not LDS reads for memory (7.5 against
+        // 8.0 ms on the large tabular forest)
+        uint4 q[4];
+        if ((uint32_t)ref < (uint32_t)fp::kGlobalRef) {
+            const lds_u32x4* lp = lds_ptr<u32x4>((uint32_t)ref * (uint32_t)ws.unit);
+#pragma unroll
+            for (int i = 0; i < bw; i++) q[i] = as_uint4(lp[i]);
+        }
+        if (ref >= fp::kGlobalRef) {
+            const global_u32x4* gp = gbase + (size_t)(uint32_t)ref * (ws.unit / 16);
+#pragma unroll
+            for (int i = 0; i < bw; i++) q[i] = as_uint4(gp[i]);
+        }
+        if (ref >= 0) {
+            bool leaf;
+            ref = walk_step<FMODE, FORM, X16>(j, q, xrow, es, row0, fmap_l, leaf);
+            if (leaf) {
+                __hip_atomic_fetch_add(const_cast<__attribute__((address_space(3))) int32_t*>(
+                                           lds_ptr<int32_t>(vrow + 4u * (uint32_t)ref)),
+                                       1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+                ref = kDone;
+            }
+        }
+    }
+    write_tile(j, vl, row0, rows_here);
+}
+
+// Stages one tile of a job of kind KIND; prefetched: the thread's first quad is `pre`.
+template <int FMODE, int KIND>
+__device__ __forceinline__ void stage_kind(const JobDesc& j, int tile, unsigned char* smem, float4 pre, bool prefetched) {
+    const int64_t row0 = (int64_t)tile * j.R;
+    stage_tile<KIND == kKind48hX || KIND == kKind32hX>(
+        j, reinterpret_cast<float*>(smem + j.off_xs), reinterpret_cast<int32_t*>(smem + j.off_votes),
+        reinterpret_cast<int32_t*>(smem + j.off_pool), row0, tile_rows(j, row0), FMODE == 1, pre, prefetched);
+}
+
+// Walks one staged tile of a job of kind KIND, K cursors per lane (block
+// layouts: one), and writes its votes.
+template <int K, int FMODE, int KIND>
+__device__ __forceinline__ void walk_tile(const JobDesc& j, int nt, int tile, unsigned char* smem) {
+    if constexpr (KIND == kKindPacked) run_tile<K, FMODE>(j, nt, tile, smem);
+    else if constexpr (KIND == kKindCompact) run_tile_compact<K, FMODE>(j, nt, tile, smem);
+    else if constexpr (KIND == kKindHost48 || KIND == kKindHost64) run_tile_blocked<1, FMODE, KIND == kKindHost48>(j, nt, tile, smem);
+    else run_tile_walk<FMODE, kind_form(KIND), KIND == kKind48hX || KIND == kKind32hX>(j, nt, tile, smem);
+}
+
 // One forest: persistent workgroups, group = blockIdx % G (consecutive
 // workgroups land on different XCDs, so G = 8 gives each XCD its own trees).
 // Waves per SIMD the kernel must allow: two 1024-thread workgroups per CU
 // (8 waves per SIMD, at most 64 VGPRs) while the cursors fit in that budget.
-// COMPACT and BLOCKED cursors carry more state (a BLOCKED one holds a
-// 64-byte block in 16 registers while it walks it).  A 1024-thread workgroup
-// needs 4 waves per SIMD, so no variant gets more than 128 VGPRs.
-template <int K, int LAYOUT>
+// A 1024-thread workgroup needs 4 waves per SIMD, so no variant gets more
+// than 128 VGPRs.
+template <int K, int KIND>
 struct MinWaves {
-    static constexpr int value = LAYOUT == FP_LAYOUT_PACKED    ? (K <= 4 ? 8 : 4)
-                                 : LAYOUT == FP_LAYOUT_COMPACT ? (K <= 2 ? 8 : 4)
-                                                               : (K == 1 ? 8 : 4);
+    static constexpr int value = KIND == kKindPacked ? (K <= 4 ? 8 : 4) : KIND == kKindCompact ? (K <= 2 ? 8 : 4) : 8;
 };
 
-template <int K, int FMODE, int LAYOUT>
-__global__ __launch_bounds__(1024, (MinWaves<K, LAYOUT>::value)) void packed_kernel(JobDesc j) {
-    extern __shared__ __align__(16) unsigned char smem[];
+template <int K, int FMODE, int KIND>
+__global__ __launch_bounds__(1024, (MinWaves<K, KIND>::value)) void packed_kernel(JobDesc j) {
+    extern __shared__ __align__(32) unsigned char smem[];
     const int group = j.group_base + (int)(blockIdx.x % j.G);
     const int blocks_per_group = gridDim.x / j.G;
-    const int nt = stage_group(j, group, smem);
+    int tile = blockIdx.x / j.G;
+    const float4 pre = prefetch_quad<FMODE>(j, tile);
+    const int nt = stage_group<KIND>(j, group, smem);
     if (nt == 0) return;  // uniform per block
-    for (int tile = blockIdx.x / j.G; tile < j.n_tiles; tile += blocks_per_group) {
-        if (LAYOUT == FP_LAYOUT_COMPACT) run_tile_compact<K, FMODE>(j, nt, tile, smem);
-        else if (LAYOUT == FP_LAYOUT_BLOCKED && j.block_bytes == 48) run_tile_blocked<K, FMODE, 0>(j, nt, tile, smem);
-        else if (LAYOUT == FP_LAYOUT_BLOCKED) run_tile_blocked<K, FMODE, 1>(j, nt, tile, smem);
-        else if (LAYOUT == FP_LAYOUT_CLUSTERED && j.block_bytes == 48) {
-            if constexpr (FMODE == 1) {
-                if (j.x16) run_tile_blocked<K, 1, 4>(j, nt, tile, smem);
-                else run_tile_blocked<K, 1, 3>(j, nt, tile, smem);
-            } else {
-                run_tile_blocked<K, FMODE, 3>(j, nt, tile, smem);
-            }
-        } else if (LAYOUT == FP_LAYOUT_CLUSTERED) run_tile_blocked<K, FMODE, 2>(j, nt, tile, smem);
-        else run_tile<K, FMODE>(j, nt, tile, smem);
+    bool first = true;
+    for (; tile < j.n_tiles; tile += blocks_per_group) {
+        stage_kind<FMODE, KIND>(j, tile, smem, pre, first);
+        first = false;
+        walk_tile<K, FMODE, KIND>(j, nt, tile, smem);
     }
 }
 
 // Many forests: persistent workgroups pull work items from a global counter
 // (items are ordered largest first) and restage LDS when the (job, group)
 // changes.  Every workgroup exits once the counter passes n_items.
+// One tile, staged and walked.
+template <int K, int FM, int KIND>
+__device__ __forceinline__ void item_tile(const JobDesc& j, int nt, int tile, unsigned char* smem) {
+    stage_kind<FM, KIND>(j, tile, smem, make_float4(0.0f, 0.0f, 0.0f, 0.0f), false);
+    walk_tile<K, FM, KIND>(j, nt, tile, smem);
+}
+
 // Tiles [tile_begin, tile_end) of one work item, features in LDS (FM 1) or
 // read from memory (FM 0).  Block layouts walk one block per lane.
 // BLOCKS: every job of the launch is in a block layout (the host picks this
@@ -981,24 +1444,28 @@ __global__ __launch_bounds__(1024, (MinWaves<K, LAYOUT>::value)) void packed_ker
 // not set the kernel's register budget.
 template <int K, int FM, bool BLOCKS>
 __device__ __forceinline__ void item_tiles(const JobDesc& j, const WorkItem& w, int nt, unsigned char* smem) {
+    const int kind = job_kind(j);
     for (int tile = w.tile_begin; tile < w.tile_end; tile++) {
-        if (!BLOCKS && j.layout == FP_LAYOUT_COMPACT) {
-            run_tile_compact<K, FM>(j, nt, tile, smem);
-        } else if (j.layout == FP_LAYOUT_CLUSTERED && j.block_bytes == 48) {
-            if constexpr (FM == 1) {
-                if (j.x16) {
-                    run_tile_blocked<1, 1, 4>(j, nt, tile, smem);
-                    continue;
-                }
-            }
-            run_tile_blocked<1, FM, 3>(j, nt, tile, smem);
-        } else if (j.layout == FP_LAYOUT_CLUSTERED) {
-            run_tile_blocked<1, FM, 2>(j, nt, tile, smem);
-        } else if (j.layout == FP_LAYOUT_BLOCKED) {
-            if (j.block_bytes == 48) run_tile_blocked<1, FM, 0>(j, nt, tile, smem);
-            else run_tile_blocked<1, FM, 1>(j, nt, tile, smem);
-        } else if constexpr (!BLOCKS) {
-            run_tile<K, FM>(j, nt, tile, smem);
+        switch (kind) {
+            case kKindPacked:
+                if constexpr (!BLOCKS) item_tile<K, FM, kKindPacked>(j, nt, tile, smem);
+                break;
+            case kKindCompact:
+                if constexpr (!BLOCKS) item_tile<K, FM, kKindCompact>(j, nt, tile, smem);
+                break;
+            case kKindHost48: item_tile<1, FM, kKindHost48>(j, nt, tile, smem); break;
+            case kKindHost64: item_tile<1, FM, kKindHost64>(j, nt, tile, smem); break;
+            case kKind64: item_tile<1, FM, kKind64>(j, nt, tile, smem); break;
+            case kKind48h: item_tile<1, FM, kKind48h>(j, nt, tile, smem); break;
+            case kKind48b: item_tile<1, FM, kKind48b>(j, nt, tile, smem); break;
+            case kKind48f: item_tile<1, FM, kKind48f>(j, nt, tile, smem); break;
+            case kKind32h: item_tile<1, FM, kKind32h>(j, nt, tile, smem); break;
+            case kKind48hX:
+                if constexpr (FM == 1) item_tile<1, 1, kKind48hX>(j, nt, tile, smem);
+                break;
+            case kKind32hX:
+                if constexpr (FM == 1) item_tile<1, 1, kKind32hX>(j, nt, tile, smem);
+                break;
         }
     }
 }
@@ -1011,7 +1478,7 @@ __global__ __launch_bounds__(1024, (K <= 2 ? 8 : 4)) void batched_kernel(const J
                                                                          const WorkItem* __restrict__ items,
                                                                          int32_t n_items, int32_t* counter,
                                                                          int32_t item_slot) {
-    extern __shared__ __align__(16) unsigned char smem[];
+    extern __shared__ __align__(32) unsigned char smem[];
     int32_t* s_item = reinterpret_cast<int32_t*>(smem + item_slot);
     int staged_job = -1, staged_group = -1, nt = 0;
     while (true) {
@@ -1026,7 +1493,7 @@ __global__ __launch_bounds__(1024, (K <= 2 ? 8 : 4)) void batched_kernel(const J
         const WorkItem w = items[it];
         const JobDesc j = jobs[w.job];
         if (w.job != staged_job || w.group != staged_group) {
-            nt = stage_group(j, w.group, smem);
+            nt = stage_group<BLOCKS ? kKindAnyBlock : kKindAny>(j, w.group, smem);
             staged_job = w.job;
             staged_group = w.group;
         }
@@ -1081,27 +1548,28 @@ int check_launch(const char* what) {
     return FP_OK;
 }
 
-template <int K, int FM, int L>
-const void* packed_fn() {
-    return reinterpret_cast<const void*>(&packed_kernel<K, FM, L>);
+template <int K, int KIND>
+const void* packed_fn(int fmode) {
+    return fmode == 0 ? reinterpret_cast<const void*>(&packed_kernel<K, 0, KIND>)
+                      : reinterpret_cast<const void*>(&packed_kernel<K, 1, KIND>);
 }
 
-template <int K, int L>
-const void* packed_fn_fm(int fmode) {
-    return fmode == 0 ? packed_fn<K, 0, L>() : packed_fn<K, 1, L>();
-}
-
-// A BLOCKED walk keeps one block in flight per lane whatever `cursors` says:
-// a second block's 16 registers halve the waves a SIMD holds, which costs more
-// than the overlap gains.
-const void* pick_packed(int K, int fmode, int layout) {
+// A block walk keeps one block in flight per lane whatever `cursors` says.
+const void* pick_packed(int K, int fmode, int kind) {
     if (K != 1 && K != 2 && K != 4 && K != 8) return nullptr;
-    if (layout == FP_LAYOUT_BLOCKED) return packed_fn_fm<1, FP_LAYOUT_BLOCKED>(fmode);
-    if (layout == FP_LAYOUT_CLUSTERED) return packed_fn_fm<1, FP_LAYOUT_CLUSTERED>(fmode);
-#define FP_PICK(KK)                                                                     \
-    if (K == KK)                                                                        \
-        return layout == FP_LAYOUT_COMPACT ? packed_fn_fm<KK, FP_LAYOUT_COMPACT>(fmode) \
-                                           : packed_fn_fm<KK, FP_LAYOUT_PACKED>(fmode);
+    switch (kind) {
+        case kKindHost48: return packed_fn<1, kKindHost48>(fmode);
+        case kKindHost64: return packed_fn<1, kKindHost64>(fmode);
+        case kKind64: return packed_fn<1, kKind64>(fmode);
+        case kKind48h: return packed_fn<1, kKind48h>(fmode);
+        case kKind48b: return packed_fn<1, kKind48b>(fmode);
+        case kKind48f: return packed_fn<1, kKind48f>(fmode);
+        case kKind32h: return packed_fn<1, kKind32h>(fmode);
+        case kKind48hX: return reinterpret_cast<const void*>(&packed_kernel<1, 1, kKind48hX>);
+        case kKind32hX: return reinterpret_cast<const void*>(&packed_kernel<1, 1, kKind32hX>);
+    }
+#define FP_PICK(KK) \
+    if (K == KK) return kind == kKindCompact ? packed_fn<KK, kKindCompact>(fmode) : packed_fn<KK, kKindPacked>(fmode);
     FP_PICK(1)
     FP_PICK(2)
     FP_PICK(4)
@@ -1164,7 +1632,7 @@ size_t default_lds_block(const DeviceProps& dp) {
 size_t job_lds_layout(JobDesc* j) {
     size_t o = 0;
     j->off_top = (int32_t)o;   o += (size_t)j->cap * j->bins_per_group * sizeof(Node16);
-    j->off_ttab = (int32_t)o;  o += (size_t)j->trees_per_group * 16;
+    j->off_ttab = (int32_t)o;  o += round16((size_t)j->trees_per_group * (j->form != kWalkNone ? 4 : 16));
     j->off_fmap = (int32_t)o;  o += j->feat_lds ? 0 : round16((size_t)j->Fc * 4);
     j->off_imap = (int32_t)o;  o += j->stage_rows ? round16((size_t)(j->F + 3) / 4 * 4 * 2) : 0;
     j->off_xs = (int32_t)o;    o += j->feat_lds ? round16(j->x16 ? (size_t)j->Fc * j->Fcp * 2 : (size_t)j->R * j->Fcp * 4) : 0;
@@ -1215,6 +1683,7 @@ int resolve_job(const fp_packed* p, const fp_tune* t, const float* X, int64_t n_
     j->Fcp = h.n_used_features | 1;
     j->C = h.n_classes;
     j->n_bins = h.n_bins;
+    j->n_trees = h.n_trees;
     j->bin_size = h.bin_size;
     j->R = R;
     j->G = G;
@@ -1226,7 +1695,8 @@ int resolve_job(const fp_packed* p, const fp_tune* t, const float* X, int64_t n_
     j->layout = h.layout;
     j->fbits = h.compact_fbits;
     j->cbits = h.compact_cbits;
-    j->block_bytes = h.block_bytes;
+    j->form = walk_form(h);
+    j->block_bytes = j->form != kWalkNone ? walk_shape(j->form).bytes : h.block_bytes;
     if (t->refill_lanes < 0 || t->refill_lanes > 64) return fp_set_error(FP_EINVAL, "refill_lanes %d outside [0, 64]", t->refill_lanes);
     j->refill_min = t->refill_lanes > 0 ? t->refill_lanes : kDefaultRefillLanes;
     // feature_lds: 1 force LDS staging, 2 force it in fp32, -1 read features
@@ -1277,7 +1747,7 @@ int resolve_job(const fp_packed* p, const fp_tune* t, const float* X, int64_t n_
     if (t->lds_top_nodes < 0 || h.layout == FP_LAYOUT_COMPACT) top_nodes = 0;  // COMPACT: tops from memory
     else if (t->lds_top_nodes > 0) top_nodes = std::min(top_nodes, (size_t)t->lds_top_nodes);
     if (h.layout >= FP_LAYOUT_BLOCKED) {
-        const size_t bw = (size_t)h.block_bytes / 16;
+        const size_t bw = (size_t)j->block_bytes / 16;
         int64_t max_blocks = 0;
         for (int32_t b = 0; b < h.n_bins; b++) max_blocks = std::max<int64_t>(max_blocks, bins_host(p)[b].deep_len);
         j->cap = (int32_t)(std::min<size_t>(top_nodes / bpg / bw, (size_t)max_blocks) * bw);
@@ -1288,11 +1758,11 @@ int resolve_job(const fp_packed* p, const fp_tune* t, const float* X, int64_t n_
     return FP_OK;
 }
 
-int packed_occupancy(int K, int fmode, int layout, int threads, size_t lds, int* blocks_per_cu) {
-    const void* fn = pick_packed(K, fmode, layout);
+int packed_occupancy(int K, const JobDesc& j, int threads, int* blocks_per_cu) {
+    const void* fn = pick_packed(K, j.feat_lds ? 1 : 0, job_kind(j));
     if (!fn) return fp_set_error(FP_EINVAL, "cursors must be 1, 2, 4 or 8");
     int occ = 0;
-    hipError_t e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&occ, fn, threads, lds);
+    hipError_t e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&occ, fn, threads, (size_t)j.lds_bytes);
     *blocks_per_cu = (e == hipSuccess && occ > 0) ? occ : 1;
     return FP_OK;
 }
@@ -1329,6 +1799,30 @@ int device_upload(void* dev, const void* src, size_t n, void* stream_v, int* dev
     if (e != hipSuccess) return fp_set_error(FP_EHIP, "hipGetDevice: %s", hipGetErrorString(e));
     e = hipMemcpyAsync(dev, src, n, hipMemcpyHostToDevice, stream);
     if (e != hipSuccess) return fp_set_error(FP_EHIP, "hipMemcpyAsync: %s", hipGetErrorString(e));
+    Header h;
+    memcpy(&h, src, sizeof h);
+    if (const int32_t form = walk_form(h); form != kWalkNone && h.n_bins > 0) {
+        uint8_t* base = static_cast<uint8_t*>(dev);
+        const BinEntry* bins = reinterpret_cast<const BinEntry*>(static_cast<const uint8_t*>(src) + h.table_offset);
+        int64_t blocks = 0;  // of the largest bin
+        for (int32_t b = 0; b < h.n_bins; b++) blocks = std::max<int64_t>(blocks, bins[b].deep_len);
+        const int64_t from = h.block_bytes, to = walk_shape(form).bytes;
+        const unsigned rows = (unsigned)std::min(h.n_bins, 65535);
+        for (int64_t lo = 0, hi; lo < blocks; lo = hi) {
+            // the blocks of one launch are written over blocks that earlier
+            // launches have read, [lo to / from, lo) when they shrink; the
+            // first 256 of a bin are one workgroup's
+            hi = from == to ? blocks : std::max<int64_t>(256, std::min(blocks, lo * from / to));
+            hipLaunchKernelGGL(walk_form_kernel, dim3((unsigned)((hi - lo + 255) / 256), rows), dim3(256), 0, stream,
+                               reinterpret_cast<const BinEntry*>(base + h.table_offset), h.n_bins,
+                               reinterpret_cast<uint32_t*>(base + h.nodes_offset), h.layout, form, h.block_bytes,
+                               h.compact_fbits, h.compact_cbits, lo, hi);
+        }
+        if (const int rc = check_launch("walk_form_kernel")) {
+            (void)hipStreamSynchronize(stream);
+            return rc;
+        }
+    }
     e = hipStreamSynchronize(stream);
     if (e != hipSuccess) return fp_set_error(FP_EHIP, "hipStreamSynchronize: %s", hipGetErrorString(e));
     return FP_OK;
@@ -1375,7 +1869,7 @@ int launch_argmax(const int32_t* votes, int32_t* cls, int64_t n, int32_t C, hipS
 }
 
 int launch_packed(const JobDesc& j, int K, int threads, int blocks, hipStream_t s) {
-    const void* fn = pick_packed(K, j.feat_lds ? 1 : 0, j.layout);
+    const void* fn = pick_packed(K, j.feat_lds ? 1 : 0, job_kind(j));
     if (!fn) return fp_set_error(FP_EINVAL, "cursors must be 1, 2, 4 or 8");
     JobDesc a = j;
     void* args[] = {&a};
@@ -1458,7 +1952,7 @@ static int predict_impl(const fp_packed* p, const fp_tune* tune, const float* X,
     rc = fp::resolve_job(p, tune, X, n_rows, ld, votes, cls, lds_block, &j);
     if (rc) return rc;
     int occ = 1;
-    rc = fp::packed_occupancy(K, j.feat_lds, j.layout, threads, (size_t)j.lds_bytes, &occ);
+    rc = fp::packed_occupancy(K, j, threads, &occ);
     if (rc) return rc;
     const int64_t per_group = std::min<int64_t>(j.n_tiles, std::max<int64_t>(1, (int64_t)dp.cus * occ / j.G));
     const int blocks = (int)std::max<int64_t>(1, per_group) * j.G;
