@@ -91,7 +91,7 @@ extern "C" int fp_predict_batched_noalloc(const fp_job* jobs, int32_t n_jobs, co
         fp_tune t = jb.forest->tune;
         fp_tune rec;
         if (jb.n_rows > 0 && fp::launch_tune_get(jb.forest, jb.n_rows, threads, K, &rec)) t = rec;
-        rc = fp::resolve_job(jb.forest, &t, jb.X, jb.n_rows, jb.ld, jb.votes, jb.cls, lds_block, &jd[i]);
+        rc = fp::resolve_job(jb.forest, &t, jb.X, jb.n_rows, jb.ld, jb.votes, jb.cls, lds_block, 0, &jd[i]);
         if (rc) return rc;
         fp::flatten_passes(&jd[i]);
         lds = std::max(lds, (size_t)jd[i].lds_bytes);

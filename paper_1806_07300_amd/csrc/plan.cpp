@@ -177,11 +177,11 @@ extern "C" int fp_plan_create(const fp_job* jobs, int32_t n_jobs, const fp_plan_
                 }
                 // candidates are timed with the default LDS budget: a smaller
                 // plan budget falls back to the forest's own parameters
-                if (fp::resolve_job(jb.forest, &t, jb.X, jb.n_rows, jb.ld, jb.votes, jb.cls, lds_block, &p->jobs[i]) ==
+                if (fp::resolve_job(jb.forest, &t, jb.X, jb.n_rows, jb.ld, jb.votes, jb.cls, lds_block, 0, &p->jobs[i]) ==
                     FP_E2BIG)
                     t = jb.forest->tune;
             }
-            rc = fp::resolve_job(jb.forest, &t, jb.X, jb.n_rows, jb.ld, jb.votes, jb.cls, lds_block, &p->jobs[i]);
+            rc = fp::resolve_job(jb.forest, &t, jb.X, jb.n_rows, jb.ld, jb.votes, jb.cls, lds_block, 0, &p->jobs[i]);
             if (rc) {
                 std::string msg = fp_last_error();
                 return fp_set_error(rc, "job %d: %s", i, msg.c_str());

@@ -50,7 +50,11 @@ using fp::WorkItem;
 namespace {
 
 constexpr int32_t kDone = INT32_MIN;
-constexpr int kDefaultRefillLanes = 16;
+// Idle lanes of a wavefront that trigger a refill.  A block step is long and
+// a refill adds two LDS round trips to it: later refills pay (40,000 rows x
+// 1,024 trees: at 16 lanes 342 us, at 48 308; 10^6 rows x 32 trees 245 and
+// 230); node steps are short (2,000 rows x 64 trees: 52 and 59 us).
+constexpr int kDefaultRefillLanes = 16, kDefaultRefillLanesBlocks = 48;
 constexpr int kStageBatch = 4;  // row loads a thread issues before scattering them (tile staging)
 
 // ---------------------------------------------------------------------------
@@ -1647,7 +1651,7 @@ const BinEntry* bins_host(const fp_packed* p) {
 }
 
 int resolve_job(const fp_packed* p, const fp_tune* t, const float* X, int64_t n_rows, int64_t ld, int32_t* votes,
-                int32_t* cls, size_t lds_block, JobDesc* j) {
+                int32_t* cls, size_t lds_block, int cus, JobDesc* j) {
     const Header& h = p->hdr;
     if (h.layout != FP_LAYOUT_PACKED && h.layout != FP_LAYOUT_COMPACT && h.layout != FP_LAYOUT_BLOCKED &&
         h.layout != FP_LAYOUT_CLUSTERED)
@@ -1655,11 +1659,18 @@ int resolve_job(const fp_packed* p, const fp_tune* t, const float* X, int64_t n_
     if (!p->dev) return fp_set_error(FP_ENODEV, "packed forest is not uploaded");
     if (h.n_nodes >= INT32_MAX)
         return fp_set_error(FP_E2BIG, "packed forest has %lld nodes (limit 2^31-1)", (long long)h.n_nodes);
-    // rows_per_block 0: start at 16 and halve until the workgroup's tables fit
+    const bool blocks = h.layout >= FP_LAYOUT_BLOCKED;
     const bool auto_R = t->rows_per_block <= 0;
-    int R = auto_R ? 16 : t->rows_per_block;
-    if (R > 4096) return fp_set_error(FP_EINVAL, "rows_per_block %d exceeds 4096", R);
-    int G = t->tree_groups > 0 ? t->tree_groups : 1;
+    if (t->rows_per_block > 4096) return fp_set_error(FP_EINVAL, "rows_per_block %d exceeds 4096", t->rows_per_block);
+    // tree_groups 0: one; for a block layout of at least 512 trees and 2^18
+    // walks launched alone (cus > 0), a group per 128 trees: a workgroup's LDS then holds several
+    // blocks of each of its trees instead of one or none (4,096 rows x 1,024
+    // trees: one group 60 us at its best tile, eight 47; 40,000 rows: 382 and
+    // 337), which pays for zeroing the votes and the classes' own launch
+    int G = t->tree_groups > 0                                                             ? t->tree_groups
+            : blocks && cus > 0 && h.n_trees >= 512 && n_rows * h.n_trees >= (1 << 18) && t->tree_passes <= 1 ? h.n_trees / 128
+                                                                                                   : 1;
+    if (t->tree_groups <= 0) G = std::min(G, 8);
     if (G > h.n_bins) G = h.n_bins;
     int P = t->tree_passes > 0 ? t->tree_passes : 1;
     if ((int64_t)P * G > h.n_bins) P = std::max(1, h.n_bins / G);
@@ -1667,6 +1678,18 @@ int resolve_job(const fp_packed* p, const fp_tune* t, const float* X, int64_t n_
     // passes that would hold no bin are dropped: the last pass writes the classes
     P = ((h.n_bins + bpg - 1) / bpg + G - 1) / G;
     const int tpg = (int)std::min<int64_t>((int64_t)bpg * h.bin_size, h.n_trees);
+    // rows_per_block 0: 16; a block layout launched alone: a tile per CU (with tree groups, per
+    // half CU and group), of at most 16,384 walks and 512 rows.  Fewer, larger
+    // tiles leave CUs idle (300 image rows x 128 trees: 16-row tiles 15.9 us,
+    // 2-row ones 10.8); smaller ones stage the trees' first blocks and wait
+    // for their last walks more often (4,096 rows x 1,024 trees: 8-row tiles
+    // 71 us, 16-row ones 60; 10^6 rows x 32 trees: 16-row tiles 558 us,
+    // 128-row ones 270, 512-row ones 241)
+    const int64_t most = std::min<int64_t>(512, std::max<int64_t>(32, 16384 / tpg));
+    int R = !auto_R  ? t->rows_per_block
+            : !blocks || cus <= 0 ? 16
+            : G > 1   ? (int)std::min(most, std::max<int64_t>(16, (n_rows * G + 2 * cus - 1) / (2 * cus)))
+                      : (int)std::min(most, std::max<int64_t>(1, (n_rows + cus - 1) / cus));
     if ((int64_t)R * tpg >= (1 << 30)) return fp_set_error(FP_E2BIG, "rows_per_block x trees per group too large");
     const uint8_t* base = static_cast<const uint8_t*>(p->dev);
     memset(j, 0, sizeof *j);
@@ -1698,7 +1721,7 @@ int resolve_job(const fp_packed* p, const fp_tune* t, const float* X, int64_t n_
     j->form = walk_form(h);
     j->block_bytes = j->form != kWalkNone ? walk_shape(j->form).bytes : h.block_bytes;
     if (t->refill_lanes < 0 || t->refill_lanes > 64) return fp_set_error(FP_EINVAL, "refill_lanes %d outside [0, 64]", t->refill_lanes);
-    j->refill_min = t->refill_lanes > 0 ? t->refill_lanes : kDefaultRefillLanes;
+    j->refill_min = t->refill_lanes > 0 ? t->refill_lanes : blocks ? kDefaultRefillLanesBlocks : kDefaultRefillLanes;
     // feature_lds: 1 force LDS staging, 2 force it in fp32, -1 read features
     // from memory, 0 automatic
     if (t->feature_lds < -1 || t->feature_lds > 2) return fp_set_error(FP_EINVAL, "feature_lds %d outside [-1, 2]", t->feature_lds);
@@ -1722,14 +1745,19 @@ int resolve_job(const fp_packed* p, const fp_tune* t, const float* X, int64_t n_
         return job_lds_layout(j);
     };
     // fit by shrinking an automatic tile first (features in LDS matter most),
-    // then by reading features from memory
+    // then by reading features from memory.  An automatic tile leaves LDS for
+    // a block per tree, up to a quarter of the budget
+    const size_t tops = auto_R && blocks ? std::min(lds_block / 4, (size_t)tpg * (size_t)j->block_bytes) : 0;
     auto fit = [&](bool feat) {
         size_t need = size_for(R, feat);
-        for (int r = R; need > lds_block && auto_R && r > 1;) {
-            r = std::max(1, r / 2);
-            need = size_for(r, feat);
+        if (!auto_R || need + (feat ? tops : 0) <= lds_block) return need;
+        int lo = 1, hi = R;  // the largest tile that fits (1 if none does)
+        while (hi - lo > 1) {
+            const int r = (lo + hi) / 2;
+            if (size_for(r, feat) + (feat ? tops : 0) <= lds_block) lo = r;
+            else hi = r;
         }
-        return need;
+        return size_for(lo, feat);
     };
     size_t need = fit(t->feature_lds >= 0);
     if (need > lds_block) {
@@ -1922,7 +1950,10 @@ static int predict_impl(const fp_packed* p, const fp_tune* tune, const float* X,
     rc = fp::device_props(dev, &dp);
     if (rc) return rc;
     hipStream_t stream = static_cast<hipStream_t>(stream_v);
-    const int threads = tune && tune->block_threads > 0 ? tune->block_threads : 256;
+    // block layouts: 16 waves a workgroup, which share its tile and first
+    // blocks (20,001 rows x 784 features x 256 trees, 16-row tiles: 256
+    // threads 142 us, 1024 threads 102)
+    const int threads = tune && tune->block_threads > 0 ? tune->block_threads : h.layout >= FP_LAYOUT_BLOCKED ? 1024 : 256;
     if (threads % 64 || threads < 64 || threads > 1024)
         return fp_set_error(FP_EINVAL, "block_threads %d must be a multiple of 64 in [64, 1024]", threads);
 
@@ -1949,12 +1980,36 @@ static int predict_impl(const fp_packed* p, const fp_tune* tune, const float* X,
                              : tune && tune->lds_top_nodes > 0 ? lds_max
                                                                : fp::default_lds_block(dp);
     fp::JobDesc j;
-    rc = fp::resolve_job(p, tune, X, n_rows, ld, votes, cls, lds_block, &j);
+    rc = fp::resolve_job(p, tune, X, n_rows, ld, votes, cls, lds_block, dp.cus, &j);
     if (rc) return rc;
     int occ = 1;
     rc = fp::packed_occupancy(K, j, threads, &occ);
     if (rc) return rc;
-    const int64_t per_group = std::min<int64_t>(j.n_tiles, std::max<int64_t>(1, (int64_t)dp.cus * occ / j.G));
+    const int64_t resident = std::max<int64_t>(1, (int64_t)dp.cus * occ / j.G);  // workgroups of a group
+    if (h.layout >= FP_LAYOUT_BLOCKED && j.n_tiles > resident) {
+        // full rounds of tiles: rows spread evenly, so that the last round
+        // does not leave most workgroups idle (2M rows in 768-row tiles, 10.2
+        // rounds of 256: 7.04 ms, 11 full ones 6.38).  An automatic tile may
+        // grow for a round less if it still fits (20,001 rows x 784 features:
+        // 3 rounds of 14 rows 113 us, 2 of 20 100)
+        const bool grow = !tune || tune->rows_per_block <= 0;
+        const int64_t rounds = (j.n_tiles + resident - 1) / resident;
+        for (int64_t r = grow && rounds <= 4 ? rounds - 1 : rounds; r <= rounds; r++) {
+            fp_tune even = tune ? *tune : fp_tune{};
+            even.rows_per_block = (int32_t)std::min<int64_t>(4096, (n_rows + r * resident - 1) / (r * resident));
+            if (even.rows_per_block == j.R || even.rows_per_block > j.R + j.R / 4) continue;
+            fp::JobDesc e;
+            int occ_e = 0;
+            if (fp::resolve_job(p, &even, X, n_rows, ld, votes, cls, lds_block, dp.cus, &e) == FP_OK &&
+                fp::packed_occupancy(K, e, threads, &occ_e) == FP_OK && e.feat_lds == j.feat_lds && e.G == j.G &&
+                occ_e == occ) {
+                j = e;
+                break;
+            }
+            fp_clear_error();
+        }
+    }
+    const int64_t per_group = std::min<int64_t>(j.n_tiles, resident);
     const int blocks = (int)std::max<int64_t>(1, per_group) * j.G;
     if (j.atomic_votes) {
         rc = fp::launch_fill(votes, n_rows * h.n_classes, 0, stream);
