@@ -327,7 +327,8 @@ size_t job_lds_layout(JobDesc* j);
 
 // Fill `j` for forest p, launch parameters t (threads and cursors decided by
 // the caller), rows X.  `lds_block` caps the job's LDS footprint (bytes); `cus`
-// > 0: the job has a launch, and that many CUs, to itself; 0: it shares one.
+// > 0: the job has a launch, and that many CUs, to itself; 0: it shares one;
+// -1: it shares one and its latency counts (serving).
 int resolve_job(const fp_packed* p, const fp_tune* t, const float* X, int64_t n_rows, int64_t ld,
                 int32_t* votes, int32_t* cls, size_t lds_block, int cus, JobDesc* j);
 
@@ -346,10 +347,17 @@ constexpr size_t kItemSlotBytes = 16;
 // workgroup took 19.8 ms, 8 16.7 ms, 16 14.8 ms, 64 14.4 ms.
 constexpr int kDefaultItemsPerBlock = 16;
 size_t batched_job_budget(size_t lds_block);
-// blocks_only: every job of the launch is in a block layout (BLOCKED or
-// CLUSTERED): the launch takes the kernel variant without node-layout walks.
-int batched_occupancy(int K, bool blocks_only, int threads, size_t lds, int* blocks_per_cu);
-bool jobs_blocks_only(const JobDesc* jobs, int32_t n_jobs);
+// A batched launch: block-layout jobs (class 0) and node-layout ones (class 1)
+// run in a kernel each, over their own part of the work list.
+struct BatchedShape {
+    int K = 2, threads = 1024;
+    int32_t n_jobs = 0;
+    size_t lds[2] = {0, 0};           // the largest job layout
+    int64_t resident[2] = {1, 1};     // workgroups that fit the device
+    bool atomics = false, atomic_classes = false;  // some job's groups add into its votes (and it wants classes)
+};
+inline int batched_class(const JobDesc& j) { return j.layout >= FP_LAYOUT_BLOCKED ? 0 : 1; }
+int batched_shape(const JobDesc* jobs, int32_t n_jobs, int K, int threads, int cus, BatchedShape* out);
 
 // The packer's two device operations, kept out of the host-only packer:
 // copy a packed buffer of n bytes to device memory on `stream`, put its
@@ -367,11 +375,11 @@ int launch_leaf_counts(const Node16* nodes, const int64_t* tree_off, int32_t n_t
                        int64_t ld, int32_t* counts, hipStream_t s);
 int launch_argmax(const int32_t* votes, int32_t* cls, int64_t n, int32_t C, hipStream_t s);
 int launch_packed(const JobDesc& j, int K, int threads, int blocks, hipStream_t s);
-int launch_batched(const JobDesc* jobs, const WorkItem* items, int32_t n_items, int32_t* counter, int K,
-                   bool blocks_only, int threads, size_t lds_bytes, int blocks, hipStream_t s);
-// Zero the work counter and the votes of every job that accumulates with atomics.
-int launch_batched_prologue(const JobDesc* jobs_dev, int32_t n_jobs, int32_t* counter, hipStream_t s);
-int launch_batched_epilogue(const JobDesc* jobs_dev, int32_t n_jobs, hipStream_t s);
+// Zeroes the votes of jobs that accumulate with atomics, walks the work list
+// and takes their classes; kernels without work are left out.  `counters`: two
+// zeros in device memory, zero again when the launch ends.
+int launch_batched(const BatchedShape& sh, const JobDesc* jobs, const WorkItem* items, int32_t n_block_items, int32_t n_items,
+                   int32_t* counters, hipStream_t s);
 
 // Launch tunes per (packed forest, batch-size bucket) and the autotuner's
 // results, in a process-wide table mirrored to the FP_TUNE_CACHE file
@@ -388,14 +396,15 @@ int search_launch(const fp_packed* p, const float* X, int64_t n_rows, int64_t ld
                   hipStream_t stream, fp_tune* best, double* best_ms, int32_t* tried);
 
 // Work list of a batched launch (plan.cpp): chunks of row tiles per (job,
-// tree group), about `items_per_block` items per resident workgroup, largest
-// estimated cost first.  `expected_depth[i]` is job i's forest cost model.
-void build_items(const std::vector<JobDesc>& jobs, const std::vector<double>& expected_depth, int64_t resident,
-                 int items_per_block, std::vector<WorkItem>* items, double* total_cost);
+// tree group), about `items_per_block` items per resident workgroup, block
+// layouts first, in each class largest estimated cost first.
+// `expected_depth[i]` is job i's forest cost model.
+void build_items(const std::vector<JobDesc>& jobs, const std::vector<double>& expected_depth, const BatchedShape& sh,
+                 int items_per_block, std::vector<WorkItem>* items, int32_t* n_block_items, double* total_cost);
 // The same into caller memory of cap items; returns the number of items
 // (sorted only when it is at most cap).  Allocates nothing.
-size_t build_items_into(const JobDesc* jobs, const double* expected_depth, size_t n, int64_t resident,
-                        int items_per_block, WorkItem* out, size_t cap, double* total_cost);
+size_t build_items_into(const JobDesc* jobs, const double* expected_depth, size_t n, const BatchedShape& sh,
+                        int items_per_block, WorkItem* out, size_t cap, int32_t* n_block_items, double* total_cost);
 
 }  // namespace fp
 

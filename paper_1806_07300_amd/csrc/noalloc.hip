@@ -3,8 +3,7 @@
 // loops).  The job table, the work list and the work counter that
 // fp_plan_create allocates for a plan live here in a file-scope device
 // array of kScratchBytes, one copy per device, held until the process ends.
-// The kernels are the batched path's (prologue, persistent kernel,
-// epilogue); only where their tables live differs.
+// The kernels are the batched path's; only where their tables live differs.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -78,7 +77,6 @@ extern "C" int fp_predict_batched_noalloc(const fp_job* jobs, int32_t n_jobs, co
     // job's launch parameters are its forest's (or a recorded tune for the
     // plan's workgroup size and cursors)
     fp::JobDesc* jd = reinterpret_cast<fp::JobDesc*>(g_host);
-    size_t lds = 0;
     for (int32_t i = 0; i < n_jobs; i++) {
         const fp_job& jb = jobs[i];
         if (!jb.forest) return fp_set_error(FP_EINVAL, "job %d: forest is NULL", i);
@@ -94,24 +92,22 @@ extern "C" int fp_predict_batched_noalloc(const fp_job* jobs, int32_t n_jobs, co
         rc = fp::resolve_job(jb.forest, &t, jb.X, jb.n_rows, jb.ld, jb.votes, jb.cls, lds_block, 0, &jd[i]);
         if (rc) return rc;
         fp::flatten_passes(&jd[i]);
-        lds = std::max(lds, (size_t)jd[i].lds_bytes);
     }
-    int occ = 1;
-    const bool blocks_only = fp::jobs_blocks_only(jd, n_jobs);
-    rc = fp::batched_occupancy(K, blocks_only, threads, lds, &occ);
+    fp::BatchedShape shape;
+    rc = fp::batched_shape(jd, n_jobs, K, threads, dp.cus, &shape);
     if (rc) return rc;
-    const int64_t resident = (int64_t)dp.cus * occ;
     // the plan's work list, written straight after the job table
     for (int32_t i = 0; i < n_jobs; i++) g_depth[i] = jobs[i].forest->hdr.expected_depth;
     fp::WorkItem* items = reinterpret_cast<fp::WorkItem*>(g_host + jobs_bytes);
     const size_t max_items = (kScratchBytes - jobs_bytes - 256) / sizeof(fp::WorkItem);
     double cost = 0.0;
-    const size_t n_items = fp::build_items_into(jd, g_depth, (size_t)n_jobs, resident, ipb, items, max_items, &cost);
+    int32_t n_block_items = 0;
+    const size_t n_items = fp::build_items_into(jd, g_depth, (size_t)n_jobs, shape, ipb, items, max_items, &n_block_items, &cost);
     if (n_items > max_items)
         return fp_set_error(FP_E2BIG, "%zu work items exceed the scratch's %zu", n_items, max_items);
     uint8_t* base = static_cast<uint8_t*>(sp);
     const size_t table_bytes = jobs_bytes + n_items * sizeof(fp::WorkItem);
-    int32_t* counter = reinterpret_cast<int32_t*>(base + kScratchBytes - 256);
+    int32_t* counters = reinterpret_cast<int32_t*>(base + kScratchBytes - 256);  // zero at load and after each launch
     // g_host is pageable, so HIP performs this copy synchronously (its
     // documented behaviour for unpinned memory): g_host may be rebuilt as
     // soon as the call returns; the copy is ordered after earlier work on
@@ -120,11 +116,5 @@ extern "C" int fp_predict_batched_noalloc(const fp_job* jobs, int32_t n_jobs, co
     if (e != hipSuccess) return fp_set_error(FP_EHIP, "hipMemcpyAsync (tables): %s", hipGetErrorString(e));
     const fp::JobDesc* jobs_dev = reinterpret_cast<const fp::JobDesc*>(base);
     const fp::WorkItem* items_dev = reinterpret_cast<const fp::WorkItem*>(base + jobs_bytes);
-    // the prologue kernel clears the counter (and the votes of atomic jobs)
-    rc = fp::launch_batched_prologue(jobs_dev, n_jobs, counter, stream);
-    if (rc) return rc;
-    const int blocks = (int)std::max<int64_t>(1, std::min<int64_t>(resident, (int64_t)n_items));
-    rc = fp::launch_batched(jobs_dev, items_dev, (int32_t)n_items, counter, K, blocks_only, threads, lds, blocks, stream);
-    if (rc) return rc;
-    return fp::launch_batched_epilogue(jobs_dev, n_jobs, stream);
+    return fp::launch_batched(shape, jobs_dev, items_dev, n_block_items, (int32_t)n_items, counters, stream);
 }

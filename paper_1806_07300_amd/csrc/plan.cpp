@@ -27,10 +27,10 @@ struct fp_plan {
     void* dev_mem = nullptr;        // [jobs | items | counter]
     JobDesc* jobs_dev = nullptr;
     WorkItem* items_dev = nullptr;
-    int32_t* counter_dev = nullptr;
-    int K = 2, threads = 1024, blocks = 1;
-    bool blocks_only = false;  // every job in a block layout: the lean kernel variant
-    size_t lds_bytes = 0;
+    int32_t* counters_dev = nullptr;
+    int K = 2, threads = 1024;
+    fp::BatchedShape shape;
+    int32_t n_block_items = 0;
     double total_cost = 0.0;
     int32_t jobs_tuned = 0, jobs_cached = 0;
     bool use_graph = true;
@@ -47,61 +47,62 @@ struct fp_plan {
 };
 
 static int enqueue(fp_plan* p, hipStream_t s) {
-    const int32_t n_jobs = (int32_t)p->jobs.size();
-    int rc = fp::launch_batched_prologue(p->jobs_dev, n_jobs, p->counter_dev, s);
-    if (rc) return rc;
-    rc = fp::launch_batched(p->jobs_dev, p->items_dev, (int32_t)p->items.size(), p->counter_dev, p->K,
-                            p->blocks_only, p->threads, p->lds_bytes, p->blocks, s);
-    if (rc) return rc;
-    return fp::launch_batched_epilogue(p->jobs_dev, n_jobs, s);
+    return fp::launch_batched(p->shape, p->jobs_dev, p->items_dev, p->n_block_items, (int32_t)p->items.size(),
+                              p->counters_dev, s);
 }
 
 namespace fp {
 
-size_t build_items_into(const JobDesc* jobs, const double* expected_depth, size_t n, int64_t resident,
-                        int items_per_block, WorkItem* out, size_t cap, double* total_cost) {
+size_t build_items_into(const JobDesc* jobs, const double* expected_depth, size_t n, const BatchedShape& sh,
+                        int items_per_block, WorkItem* out, size_t cap, int32_t* n_block_items, double* total_cost) {
     auto depth = [&](size_t i) { return std::max(1.0, expected_depth[i]); };
     auto tile_cost = [&](size_t i) { return (double)jobs[i].R * jobs[i].trees_per_group * depth(i); };
-    double total = 0.0;
+    double total[2] = {0.0, 0.0};
     for (size_t i = 0; i < n; i++) {
         const JobDesc& j = jobs[i];
         const int64_t trees = std::min<int64_t>((int64_t)j.n_bins * j.bin_size, (int64_t)j.trees_per_group * j.G);
-        total += (double)j.n_rows * trees * depth(i);
+        total[batched_class(j)] += (double)j.n_rows * trees * depth(i);
     }
-    const double target = total / (double)std::max<int64_t>(1, resident * std::max(1, items_per_block));
-    size_t k = 0;
-    for (size_t i = 0; i < n; i++) {
-        const JobDesc& j = jobs[i];
-        if (j.n_rows == 0) continue;
-        const int chunk =
-            (int)std::max(1.0, std::min((double)j.n_tiles, std::floor(target / std::max(tile_cost(i), 1.0))));
-        for (int32_t g = 0; g < j.G; g++) {
-            if (g * j.bins_per_group >= j.n_bins) break;
-            for (int32_t t = 0; t < j.n_tiles; t += chunk, k++)
-                if (k < cap) out[k] = WorkItem{(int32_t)i, g, t, std::min(j.n_tiles, t + chunk)};
+    size_t k = 0, k_block = 0;
+    for (int c = 0; c < 2; c++) {
+        const double target = total[c] / (double)std::max<int64_t>(1, sh.resident[c] * std::max(1, items_per_block));
+        for (size_t i = 0; i < n; i++) {
+            const JobDesc& j = jobs[i];
+            if (batched_class(j) != c || j.n_rows == 0) continue;
+            const int chunk =
+                (int)std::max(1.0, std::min((double)j.n_tiles, std::floor(target / std::max(tile_cost(i), 1.0))));
+            for (int32_t g = 0; g < j.G; g++) {
+                if (g * j.bins_per_group >= j.n_bins) break;
+                for (int32_t t = 0; t < j.n_tiles; t += chunk, k++)
+                    if (k < cap) out[k] = WorkItem{(int32_t)i, g, t, std::min(j.n_tiles, t + chunk)};
+            }
         }
+        if (c == 0) k_block = k;
     }
-    *total_cost = total;
+    *n_block_items = (int32_t)k_block;
+    *total_cost = total[0] + total[1];
     if (k > cap) return k;
-    // largest estimated cost first; equal costs keep the order of creation
-    // (job, group, first tile), so the list is the same on every call
-    std::sort(out, out + k, [&](const WorkItem& a, const WorkItem& b) {
+    // in each class largest estimated cost first; equal costs keep the order
+    // of creation (job, group, first tile), so the list is the same on every call
+    auto larger = [&](const WorkItem& a, const WorkItem& b) {
         const double ca = tile_cost(a.job) * (a.tile_end - a.tile_begin);
         const double cb = tile_cost(b.job) * (b.tile_end - b.tile_begin);
         if (ca != cb) return ca > cb;
         if (a.job != b.job) return a.job < b.job;
         if (a.group != b.group) return a.group < b.group;
         return a.tile_begin < b.tile_begin;
-    });
+    };
+    std::sort(out, out + k_block, larger);
+    std::sort(out + k_block, out + k, larger);
     return k;
 }
 
-void build_items(const std::vector<JobDesc>& jobs, const std::vector<double>& expected_depth, int64_t resident,
-                 int items_per_block, std::vector<WorkItem>* items, double* total_cost) {
-    const size_t k = build_items_into(jobs.data(), expected_depth.data(), jobs.size(), resident, items_per_block,
-                                      nullptr, 0, total_cost);
+void build_items(const std::vector<JobDesc>& jobs, const std::vector<double>& expected_depth, const BatchedShape& sh,
+                 int items_per_block, std::vector<WorkItem>* items, int32_t* n_block_items, double* total_cost) {
+    const size_t k = build_items_into(jobs.data(), expected_depth.data(), jobs.size(), sh, items_per_block, nullptr, 0,
+                                      n_block_items, total_cost);
     items->resize(k);
-    build_items_into(jobs.data(), expected_depth.data(), jobs.size(), resident, items_per_block, items->data(), k,
+    build_items_into(jobs.data(), expected_depth.data(), jobs.size(), sh, items_per_block, items->data(), k, n_block_items,
                      total_cost);
 }
 
@@ -187,18 +188,13 @@ extern "C" int fp_plan_create(const fp_job* jobs, int32_t n_jobs, const fp_plan_
                 return fp_set_error(rc, "job %d: %s", i, msg.c_str());
             }
             fp::flatten_passes(&p->jobs[i]);
-            p->lds_bytes = std::max(p->lds_bytes, (size_t)p->jobs[i].lds_bytes);
             depth[i] = h.expected_depth;
         }
 
         // 2) persistent grid and work items
-        int occ = 1;
-        p->blocks_only = fp::jobs_blocks_only(p->jobs.data(), (int32_t)p->jobs.size());
-        rc = fp::batched_occupancy(p->K, p->blocks_only, p->threads, p->lds_bytes, &occ);
+        rc = fp::batched_shape(p->jobs.data(), n_jobs, p->K, p->threads, dp.cus, &p->shape);
         if (rc) return rc;
-        const int64_t resident = (int64_t)dp.cus * occ;
-        fp::build_items(p->jobs, depth, resident, items_per_block, &p->items, &p->total_cost);
-        p->blocks = (int)std::max<int64_t>(1, std::min<int64_t>(resident, (int64_t)p->items.size()));
+        fp::build_items(p->jobs, depth, p->shape, items_per_block, &p->items, &p->n_block_items, &p->total_cost);
 
         // 3) device tables
         const size_t jobs_b = sizeof(JobDesc) * p->jobs.size();
@@ -211,7 +207,9 @@ extern "C" int fp_plan_create(const fp_job* jobs, int32_t n_jobs, const fp_plan_
         uint8_t* base = static_cast<uint8_t*>(p->dev_mem);
         p->jobs_dev = reinterpret_cast<JobDesc*>(base);
         p->items_dev = reinterpret_cast<WorkItem*>(base + items_off);
-        p->counter_dev = reinterpret_cast<int32_t*>(base + counter_off);
+        p->counters_dev = reinterpret_cast<int32_t*>(base + counter_off);
+        const int32_t zeros[2] = {0, 0};
+        HIPCHK(hipMemcpy(p->counters_dev, zeros, sizeof zeros, hipMemcpyHostToDevice));
         HIPCHK(hipMemcpy(p->jobs_dev, p->jobs.data(), jobs_b, hipMemcpyHostToDevice));
         if (!p->items.empty())
             HIPCHK(hipMemcpy(p->items_dev, p->items.data(), sizeof(WorkItem) * p->items.size(), hipMemcpyHostToDevice));
@@ -258,11 +256,13 @@ extern "C" int fp_plan_info_get(const fp_plan* p, fp_plan_info* out) {
     memset(out, 0, sizeof *out);
     out->n_jobs = (int32_t)p->jobs.size();
     out->n_items = (int32_t)p->items.size();
-    out->blocks = p->blocks;
+    const int64_t n_node_items = (int64_t)p->items.size() - p->n_block_items;
+    out->blocks = (int32_t)std::max<int64_t>(1, std::max(std::min<int64_t>(p->shape.resident[0], p->n_block_items),
+                                                         std::min<int64_t>(p->shape.resident[1], n_node_items)));
     out->block_threads = p->threads;
     out->cursors = p->K;
     out->graph = p->exec != nullptr;
-    out->lds_bytes = (int32_t)p->lds_bytes;
+    out->lds_bytes = (int32_t)std::max(p->shape.lds[0], p->shape.lds[1]);
     out->total_cost = p->total_cost;
     out->jobs_tuned = p->jobs_tuned;
     out->jobs_cached = p->jobs_cached;

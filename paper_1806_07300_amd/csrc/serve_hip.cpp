@@ -97,6 +97,9 @@ class HipExecutor final : public fp::ServeExecutor {
             e = hipMalloc(&sl.d_tables, kTableBytes);
             if (e == hipSuccess) e = hipHostMalloc(&sl.h_tables, kTableBytes, hipHostMallocDefault);
             if (e != hipSuccess) return fp_set_error(FP_ENOMEM, "slot tables: %s", hipGetErrorString(e));
+            const int32_t zeros[2] = {0, 0};  // the work counters
+            e = hipMemcpy(static_cast<uint8_t*>(sl.d_tables) + kTableBytes - kAlign, zeros, sizeof zeros, hipMemcpyHostToDevice);
+            if (e != hipSuccess) return fp_set_error(FP_EHIP, "slot tables: %s", hipGetErrorString(e));
         }
         return FP_OK;
     }
@@ -110,7 +113,7 @@ class HipExecutor final : public fp::ServeExecutor {
         if (p->dev_id != dev_) return fp_set_error(FP_ENODEV, "forest on device %d, server on device %d", p->dev_id, dev_);
         fp::JobDesc j;  // the forest's launch parameters must fit the server's LDS budget
         fp_tune t = p->tune;
-        return fp::resolve_job(p, &t, nullptr, 1, p->hdr.n_features, nullptr, nullptr, lds_block_, 0, &j);
+        return fp::resolve_job(p, &t, nullptr, 1, p->hdr.n_features, nullptr, nullptr, lds_block_, -1, &j);
     }
 
     void bind_thread() override { (void)hipSetDevice(dev_); }
@@ -119,34 +122,31 @@ class HipExecutor final : public fp::ServeExecutor {
         HipSlot& s = slots_[slot];
         std::vector<fp::JobDesc> jobs(batch.size());
         std::vector<double> depth(batch.size());
-        size_t lds = 0;
         for (size_t i = 0; i < batch.size(); i++) {
             const fp::ServeItem& r = batch[i];
             fp_tune t = r.packed->tune;
             int rc = fp::resolve_job(r.packed, &t, reinterpret_cast<const float*>(d_x_ + r.x_start), r.n_rows, r.F,
-                                     reinterpret_cast<int32_t*>(d_v_ + r.v_start), nullptr, lds_block_, 0, &jobs[i]);
+                                     reinterpret_cast<int32_t*>(d_v_ + r.v_start), nullptr, lds_block_, -1, &jobs[i]);
             if (rc) return rc;
             fp::flatten_passes(&jobs[i]);
-            lds = std::max(lds, (size_t)jobs[i].lds_bytes);
             depth[i] = r.packed->hdr.expected_depth;
         }
-        int occ = 1;
-        const bool blocks_only = fp::jobs_blocks_only(jobs.data(), (int32_t)jobs.size());
-        int rc = fp::batched_occupancy(opts_.cursors, blocks_only, opts_.block_threads, lds, &occ);
+        fp::BatchedShape shape;
+        int rc = fp::batched_shape(jobs.data(), (int32_t)jobs.size(), opts_.cursors, opts_.block_threads, dp_.cus, &shape);
         if (rc) return rc;
-        const int64_t resident = (int64_t)dp_.cus * occ;
         std::vector<fp::WorkItem> items;
         double cost = 0;
+        int32_t n_block_items = 0;
         const size_t jobs_bytes = align_up(jobs.size() * sizeof(fp::JobDesc));
         for (int ipb = 4;; ipb /= 2) {
-            fp::build_items(jobs, depth, resident, ipb, &items, &cost);
+            fp::build_items(jobs, depth, shape, ipb, &items, &n_block_items, &cost);
             if (jobs_bytes + items.size() * sizeof(fp::WorkItem) + kAlign <= kTableBytes) break;
             if (ipb == 1) return fp_set_error(FP_E2BIG, "launch tables exceed %zu bytes", kTableBytes);
         }
         memcpy(s.h_tables, jobs.data(), jobs.size() * sizeof(fp::JobDesc));
         memcpy(static_cast<uint8_t*>(s.h_tables) + jobs_bytes, items.data(), items.size() * sizeof(fp::WorkItem));
         uint8_t* dt = static_cast<uint8_t*>(s.d_tables);
-        int32_t* counter = reinterpret_cast<int32_t*>(dt + kTableBytes - kAlign);
+        int32_t* counters = reinterpret_cast<int32_t*>(dt + kTableBytes - kAlign);
         hipError_t e = hipMemcpyAsync(dt, s.h_tables, jobs_bytes + items.size() * sizeof(fp::WorkItem),
                                       hipMemcpyHostToDevice, s.stream);
         // rows: one copy per run of adjacent ring blocks
@@ -163,11 +163,7 @@ class HipExecutor final : public fp::ServeExecutor {
         }
         const fp::JobDesc* jobs_dev = reinterpret_cast<const fp::JobDesc*>(dt);
         const fp::WorkItem* items_dev = reinterpret_cast<const fp::WorkItem*>(dt + jobs_bytes);
-        rc = fp::launch_batched_prologue(jobs_dev, (int32_t)jobs.size(), counter, s.stream);
-        const int blocks = (int)std::max<int64_t>(1, std::min<int64_t>(resident, (int64_t)items.size()));
-        if (!rc)
-            rc = fp::launch_batched(jobs_dev, items_dev, (int32_t)items.size(), counter, opts_.cursors, blocks_only,
-                                    opts_.block_threads, lds, blocks, s.stream);
+        rc = fp::launch_batched(shape, jobs_dev, items_dev, n_block_items, (int32_t)items.size(), counters, s.stream);
         if (rc) {
             (void)hipStreamSynchronize(s.stream);
             return rc;

@@ -417,10 +417,10 @@ struct TileRows {
 // What a kernel walks: a node layout, blocks in their host form, or blocks in
 // a walk form (with an fp16 tile: X); one kernel each, so that a launch
 // fetches only its own code and the compiler knows the block's shape.
-// kKindAny, kKindAnyBlock: decided per job (batched launches).
+// kKindAnyNode, kKindAnyBlock: decided per job (batched launches).
 enum Kind : int {
     kKindPacked, kKindCompact, kKindHost48, kKindHost64, kKind64, kKind48h, kKind48hX, kKind48b, kKind48f, kKind32h,
-    kKind32hX, kKindAny, kKindAnyBlock
+    kKind32hX, kKindAnyNode, kKindAnyBlock
 };
 constexpr int32_t kind_form(int kind) {
     return kind == kKind64                           ? (int32_t)fp::kWalk64
@@ -488,9 +488,9 @@ __device__ __forceinline__ int stage_group(const JobDesc& j, int group, unsigned
     int4* ttab = reinterpret_cast<int4*>(smem + j.off_ttab);
     const int t_lo = b_lo * j.bin_size;
     const int nt = (int)min((int64_t)b_hi * j.bin_size, (int64_t)j.n_trees) - t_lo;
-    constexpr bool any = KIND == kKindAny || KIND == kKindAnyBlock;
-    const bool blk = KIND == kKindAny ? j.layout >= FP_LAYOUT_BLOCKED : KIND != kKindPacked && KIND != kKindCompact;
-    const int32_t form = any ? j.form : kind_form(KIND);
+    constexpr bool any = KIND == kKindAnyNode || KIND == kKindAnyBlock;
+    constexpr bool blk = KIND != kKindPacked && KIND != kKindCompact && KIND != kKindAnyNode;
+    const int32_t form = KIND == kKindAnyBlock ? j.form : kind_form(KIND);
     // PACKED: the bin's top nodes; block layouts: its first blocks (roots
     // first), as 16-byte pieces; cap pieces per bin
     const int bw = !blk ? 1 : any || form == fp::kWalkNone ? j.block_bytes / 16 : fp::walk_shape(form).bytes / 16;
@@ -1443,33 +1443,32 @@ __device__ __forceinline__ void item_tile(const JobDesc& j, int nt, int tile, un
 
 // Tiles [tile_begin, tile_end) of one work item, features in LDS (FM 1) or
 // read from memory (FM 0).  Block layouts walk one block per lane.
-// BLOCKS: every job of the launch is in a block layout (the host picks this
-// variant only then), so the node-layout walks are not compiled in and do
-// not set the kernel's register budget.
+// BLOCKS: the job is in a block layout, else in a node layout: one kernel
+// each, so that neither sets the other's register budget (a mixed list of
+// jobs in one kernel spilled its walks: 64 forests 42 ms against 15).
 template <int K, int FM, bool BLOCKS>
 __device__ __forceinline__ void item_tiles(const JobDesc& j, const WorkItem& w, int nt, unsigned char* smem) {
     const int kind = job_kind(j);
     for (int tile = w.tile_begin; tile < w.tile_end; tile++) {
-        switch (kind) {
-            case kKindPacked:
-                if constexpr (!BLOCKS) item_tile<K, FM, kKindPacked>(j, nt, tile, smem);
-                break;
-            case kKindCompact:
-                if constexpr (!BLOCKS) item_tile<K, FM, kKindCompact>(j, nt, tile, smem);
-                break;
-            case kKindHost48: item_tile<1, FM, kKindHost48>(j, nt, tile, smem); break;
-            case kKindHost64: item_tile<1, FM, kKindHost64>(j, nt, tile, smem); break;
-            case kKind64: item_tile<1, FM, kKind64>(j, nt, tile, smem); break;
-            case kKind48h: item_tile<1, FM, kKind48h>(j, nt, tile, smem); break;
-            case kKind48b: item_tile<1, FM, kKind48b>(j, nt, tile, smem); break;
-            case kKind48f: item_tile<1, FM, kKind48f>(j, nt, tile, smem); break;
-            case kKind32h: item_tile<1, FM, kKind32h>(j, nt, tile, smem); break;
-            case kKind48hX:
-                if constexpr (FM == 1) item_tile<1, 1, kKind48hX>(j, nt, tile, smem);
-                break;
-            case kKind32hX:
-                if constexpr (FM == 1) item_tile<1, 1, kKind32hX>(j, nt, tile, smem);
-                break;
+        if constexpr (!BLOCKS) {
+            if (kind == kKindCompact) item_tile<K, FM, kKindCompact>(j, nt, tile, smem);
+            else item_tile<K, FM, kKindPacked>(j, nt, tile, smem);
+        } else {
+            switch (kind) {
+                case kKindHost48: item_tile<1, FM, kKindHost48>(j, nt, tile, smem); break;
+                case kKindHost64: item_tile<1, FM, kKindHost64>(j, nt, tile, smem); break;
+                case kKind64: item_tile<1, FM, kKind64>(j, nt, tile, smem); break;
+                case kKind48h: item_tile<1, FM, kKind48h>(j, nt, tile, smem); break;
+                case kKind48b: item_tile<1, FM, kKind48b>(j, nt, tile, smem); break;
+                case kKind48f: item_tile<1, FM, kKind48f>(j, nt, tile, smem); break;
+                case kKind32h: item_tile<1, FM, kKind32h>(j, nt, tile, smem); break;
+                case kKind48hX:
+                    if constexpr (FM == 1) item_tile<1, 1, kKind48hX>(j, nt, tile, smem);
+                    break;
+                case kKind32hX:
+                    if constexpr (FM == 1) item_tile<1, 1, kKind32hX>(j, nt, tile, smem);
+                    break;
+            }
         }
     }
 }
@@ -1477,11 +1476,14 @@ __device__ __forceinline__ void item_tiles(const JobDesc& j, const WorkItem& w, 
 // The item number is broadcast through a slot at the end of the dynamic LDS
 // (item_slot bytes in), not a static __shared__ variable: static LDS would
 // add to every job's budget and leave two workgroups no longer fitting a CU.
+// Every workgroup draws one number past the list; the last of them, which
+// draws n_items + gridDim.x - 1, sets the counter back to 0 for the next
+// launch, so no kernel has to clear it first.
 template <int K, bool BLOCKS>
-__global__ __launch_bounds__(1024, (K <= 2 ? 8 : 4)) void batched_kernel(const JobDesc* __restrict__ jobs,
-                                                                         const WorkItem* __restrict__ items,
-                                                                         int32_t n_items, int32_t* counter,
-                                                                         int32_t item_slot) {
+__global__ __launch_bounds__(1024, (BLOCKS || K <= 2 ? 8 : 4)) void batched_kernel(const JobDesc* __restrict__ jobs,
+                                                                                   const WorkItem* __restrict__ items,
+                                                                                   int32_t n_items, int32_t* counter,
+                                                                                   int32_t item_slot) {
     extern __shared__ __align__(32) unsigned char smem[];
     int32_t* s_item = reinterpret_cast<int32_t*>(smem + item_slot);
     int staged_job = -1, staged_group = -1, nt = 0;
@@ -1493,11 +1495,14 @@ __global__ __launch_bounds__(1024, (K <= 2 ? 8 : 4)) void batched_kernel(const J
         // registers instead of occupying vector registers in every lane
         const int it = __builtin_amdgcn_readfirstlane(*s_item);
         __syncthreads();
-        if (it >= n_items) break;
+        if (it >= n_items) {
+            if (threadIdx.x == 0 && it == n_items + (int)gridDim.x - 1) atomicExch(counter, 0);
+            break;
+        }
         const WorkItem w = items[it];
-        const JobDesc j = jobs[w.job];
+        const JobDesc& j = jobs[w.job];
         if (w.job != staged_job || w.group != staged_group) {
-            nt = stage_group<BLOCKS ? kKindAnyBlock : kKindAny>(j, w.group, smem);
+            nt = stage_group<BLOCKS ? kKindAnyBlock : kKindAnyNode>(j, w.group, smem);
             staged_job = w.job;
             staged_group = w.group;
         }
@@ -1523,10 +1528,9 @@ __global__ void argmax_kernel(const int32_t* votes, int32_t* cls, int64_t n, int
     }
 }
 
-// blockIdx.y = job: zero the votes of jobs that accumulate with atomics;
-// block (0, 0) also clears the work counter.
-__global__ void batched_prologue_kernel(const JobDesc* jobs, int32_t* counter) {
-    if (blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x == 0) *counter = 0;
+// blockIdx.y = job: zero the votes of jobs that accumulate with atomics (run
+// only when the launch has any, as is the epilogue).
+__global__ void batched_prologue_kernel(const JobDesc* jobs) {
     const JobDesc& j = jobs[blockIdx.y];
     if (!j.atomic_votes) return;
     const int64_t n = j.n_rows * j.C;
@@ -1582,11 +1586,11 @@ const void* pick_packed(int K, int fmode, int kind) {
     return nullptr;
 }
 
-// blocks_only: every job is in a block layout, which walks one block per
-// lane whatever K is.
-const void* pick_batched(int K, bool blocks_only) {
+// The batched kernel of block layouts (which walk one block per lane whatever
+// K is) or of node layouts.
+const void* pick_batched(int K, bool blocks) {
     if (K != 1 && K != 2 && K != 4 && K != 8) return nullptr;
-    if (blocks_only) return reinterpret_cast<const void*>(&batched_kernel<1, true>);
+    if (blocks) return reinterpret_cast<const void*>(&batched_kernel<1, true>);
     switch (K) {
         case 1: return reinterpret_cast<const void*>(&batched_kernel<1, false>);
         case 2: return reinterpret_cast<const void*>(&batched_kernel<2, false>);
@@ -1686,8 +1690,12 @@ int resolve_job(const fp_packed* p, const fp_tune* t, const float* X, int64_t n_
     // 71 us, 16-row ones 60; 10^6 rows x 32 trees: 16-row tiles 558 us,
     // 128-row ones 270, 512-row ones 241)
     const int64_t most = std::min<int64_t>(512, std::max<int64_t>(32, 16384 / tpg));
-    int R = !auto_R  ? t->rows_per_block
-            : !blocks || cus <= 0 ? 16
+    // A job of a plan shares the device: 16 to 64 rows, 64 tiles or more (16
+    // forests of up to 512 trees and 60,000 rows: 16-row tiles 488 us, 32-row
+    // ones 393, 64-row ones 333; 8 forests, 10,000 rows: 78, 58 and 58)
+    int R = !auto_R               ? t->rows_per_block
+            : !blocks || cus < 0 ? 16
+            : cus == 0           ? (int)std::min<int64_t>(64, std::max<int64_t>(16, n_rows / 64))
             : G > 1   ? (int)std::min(most, std::max<int64_t>(16, (n_rows * G + 2 * cus - 1) / (2 * cus)))
                       : (int)std::min(most, std::max<int64_t>(1, (n_rows + cus - 1) / cus));
     if ((int64_t)R * tpg >= (1 << 30)) return fp_set_error(FP_E2BIG, "rows_per_block x trees per group too large");
@@ -1746,8 +1754,8 @@ int resolve_job(const fp_packed* p, const fp_tune* t, const float* X, int64_t n_
     };
     // fit by shrinking an automatic tile first (features in LDS matter most),
     // then by reading features from memory.  An automatic tile leaves LDS for
-    // a block per tree, up to a quarter of the budget
-    const size_t tops = auto_R && blocks ? std::min(lds_block / 4, (size_t)tpg * (size_t)j->block_bytes) : 0;
+    // a block per tree, up to an eighth of the budget
+    const size_t tops = auto_R && blocks ? std::min(lds_block / 8, (size_t)tpg * (size_t)j->block_bytes) : 0;
     auto fit = [&](bool feat) {
         size_t need = size_for(R, feat);
         if (!auto_R || need + (feat ? tops : 0) <= lds_block) return need;
@@ -1795,20 +1803,29 @@ int packed_occupancy(int K, const JobDesc& j, int threads, int* blocks_per_cu) {
     return FP_OK;
 }
 
-bool jobs_blocks_only(const JobDesc* jobs, int32_t n_jobs) {
-    for (int32_t i = 0; i < n_jobs; i++)
-        if (jobs[i].layout < FP_LAYOUT_BLOCKED) return false;
-    return true;
-}
-
 size_t batched_job_budget(size_t lds_block) { return lds_block > kItemSlotBytes ? lds_block - kItemSlotBytes : 0; }
 
-int batched_occupancy(int K, bool blocks_only, int threads, size_t lds, int* blocks_per_cu) {
-    const void* fn = pick_batched(K, blocks_only);
-    if (!fn) return fp_set_error(FP_EINVAL, "cursors must be 1, 2, 4 or 8");
-    int occ = 0;
-    hipError_t e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&occ, fn, threads, round16(lds) + kItemSlotBytes);
-    *blocks_per_cu = (e == hipSuccess && occ > 0) ? occ : 1;
+int batched_shape(const JobDesc* jobs, int32_t n_jobs, int K, int threads, int cus, BatchedShape* sh) {
+    *sh = BatchedShape{};
+    sh->K = K;
+    sh->threads = threads;
+    sh->n_jobs = n_jobs;
+    bool any[2] = {false, false};
+    for (int32_t i = 0; i < n_jobs; i++) {
+        const int c = batched_class(jobs[i]);
+        any[c] = true;
+        sh->lds[c] = std::max(sh->lds[c], (size_t)jobs[i].lds_bytes);
+        sh->atomics |= jobs[i].atomic_votes != 0;
+        sh->atomic_classes |= jobs[i].atomic_votes != 0 && jobs[i].cls != nullptr;
+    }
+    for (int c = 0; c < 2; c++) {
+        const void* fn = pick_batched(K, c == 0);
+        if (!fn) return fp_set_error(FP_EINVAL, "cursors must be 1, 2, 4 or 8");
+        if (!any[c]) continue;
+        int occ = 0;
+        hipError_t e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&occ, fn, threads, round16(sh->lds[c]) + kItemSlotBytes);
+        sh->resident[c] = (int64_t)cus * ((e == hipSuccess && occ > 0) ? occ : 1);
+    }
     return FP_OK;
 }
 
@@ -1906,25 +1923,30 @@ int launch_packed(const JobDesc& j, int K, int threads, int blocks, hipStream_t 
     return FP_OK;
 }
 
-int launch_batched(const JobDesc* jobs, const WorkItem* items, int32_t n_items, int32_t* counter, int K,
-                   bool blocks_only, int threads, size_t lds_bytes, int blocks, hipStream_t s) {
-    const void* fn = pick_batched(K, blocks_only);
-    if (!fn) return fp_set_error(FP_EINVAL, "cursors must be 1, 2, 4 or 8");
-    int32_t item_slot = (int32_t)round16(lds_bytes);
-    void* args[] = {&jobs, &items, &n_items, &counter, &item_slot};
-    hipError_t e = hipLaunchKernel(fn, dim3(blocks), dim3(threads), args, (size_t)item_slot + kItemSlotBytes, s);
-    if (e != hipSuccess) return fp_set_error(FP_EHIP, "batched_kernel launch: %s", hipGetErrorString(e));
+int launch_batched(const BatchedShape& sh, const JobDesc* jobs, const WorkItem* items, int32_t n_block_items, int32_t n_items,
+                   int32_t* counters, hipStream_t s) {
+    if (sh.atomics) {
+        hipLaunchKernelGGL(batched_prologue_kernel, dim3(64, sh.n_jobs), dim3(256), 0, s, jobs);
+        if (const int rc = check_launch("batched_prologue_kernel")) return rc;
+    }
+    for (int c = 0; c < 2; c++) {
+        const WorkItem* list = items + (c == 0 ? 0 : n_block_items);
+        int32_t n = c == 0 ? n_block_items : n_items - n_block_items;
+        if (n == 0) continue;
+        const void* fn = pick_batched(sh.K, c == 0);
+        if (!fn) return fp_set_error(FP_EINVAL, "cursors must be 1, 2, 4 or 8");
+        int32_t item_slot = (int32_t)round16(sh.lds[c]);
+        int32_t* counter = counters + c;
+        void* args[] = {&jobs, &list, &n, &counter, &item_slot};
+        const int blocks = (int)std::max<int64_t>(1, std::min<int64_t>(sh.resident[c], n));
+        hipError_t e = hipLaunchKernel(fn, dim3(blocks), dim3(sh.threads), args, (size_t)item_slot + kItemSlotBytes, s);
+        if (e != hipSuccess) return fp_set_error(FP_EHIP, "batched_kernel launch: %s", hipGetErrorString(e));
+    }
+    if (sh.atomic_classes) {
+        hipLaunchKernelGGL(batched_epilogue_kernel, dim3(64, sh.n_jobs), dim3(256), 0, s, jobs);
+        return check_launch("batched_epilogue_kernel");
+    }
     return FP_OK;
-}
-
-int launch_batched_prologue(const JobDesc* jobs_dev, int32_t n_jobs, int32_t* counter, hipStream_t s) {
-    hipLaunchKernelGGL(batched_prologue_kernel, dim3(64, n_jobs), dim3(256), 0, s, jobs_dev, counter);
-    return check_launch("batched_prologue_kernel");
-}
-
-int launch_batched_epilogue(const JobDesc* jobs_dev, int32_t n_jobs, hipStream_t s) {
-    hipLaunchKernelGGL(batched_epilogue_kernel, dim3(64, n_jobs), dim3(256), 0, s, jobs_dev);
-    return check_launch("batched_epilogue_kernel");
 }
 
 }  // namespace fp
