@@ -291,7 +291,8 @@ struct JobDesc {
     int32_t group_base;        // first group of this launch: workgroup b walks group group_base + b % G
     int32_t accumulate;        // 1: add the tile's votes to the stored ones (a later pass)
     int32_t form;              // WalkForm of the device copy's blocks
-    int32_t n_trees, pad_job;
+    int32_t n_trees;
+    int32_t n_nodes;           // entries of the node section
 };
 
 // A job whose groups run in several passes, flattened for launches where all

@@ -561,8 +561,15 @@ __device__ __forceinline__ int stage_group(const JobDesc& j, int group, unsigned
 }
 
 // FMODE: 0 features from memory, 1 features in LDS, 2 decided by j.feat_lds.
+// A deep node is fetched with the one that follows it in Stat order, the
+// likely next of its walk: a line fetched from beyond L1 costs 2.4 cycles of
+// the CU (L2) to 11 (beyond), a further 16 bytes of it 0.7 (100,003 rows x 64
+// trees at their best tiles: single nodes 238 us, two 214, three 239, four
+// 253; 2,000 rows: 18.0, 15.2, 14.6, 15.0).  Four cursors or more per lane
+// have no registers for that and fetch single nodes.
 template <int K, int FMODE>
 __device__ __forceinline__ void run_tile(const JobDesc& j, int nt, int tile, unsigned char* smem) {
+    constexpr int kRun = K <= 2 ? 2 : 1;
     const bool feat_lds = FMODE == 2 ? (j.feat_lds != 0) : (FMODE == 1);
     const Node16* top = reinterpret_cast<const Node16*>(smem + j.off_top);
     const int4* ttab = reinterpret_cast<const int4*>(smem + j.off_ttab);
@@ -601,14 +608,31 @@ __device__ __forceinline__ void run_tile(const JobDesc& j, int nt, int tile, uns
             if (drained) break;
             continue;
         }
-        Node16 nd[K];
+        // a top node from LDS, or kRun consecutive nodes from memory (the last
+        // node of the section repeated past its end)
+        Node16 nd[K][kRun];
 #pragma unroll
         for (int k = 0; k < K; k++)
-            if (ref[k] >= 0) nd[k] = ref[k] < cp[k] ? top[lb[k] + ref[k]] : j.nodes[gb[k] + ref[k]];
+            if (ref[k] >= 0 && ref[k] < cp[k]) nd[k][0] = top[lb[k] + ref[k]];
+#pragma unroll
+        for (int k = 0; k < K; k++)
+            if (ref[k] >= 0 && ref[k] >= cp[k]) {
+#pragma unroll
+                for (int i = 0; i < kRun; i++) nd[k][i] = j.nodes[i == 0 ? gb[k] + ref[k] : min(gb[k] + ref[k] + i, j.n_nodes - 1)];
+            }
 #pragma unroll
         for (int k = 0; k < K; k++) {
             if (ref[k] >= 0) {
-                int32_t nr = (tr.x(rowk[k], nd[k].feat) <= nd[k].thr) ? nd[k].left : nd[k].right;
+                int32_t nr = (tr.x(rowk[k], nd[k][0].feat) <= nd[k][0].thr) ? nd[k][0].left : nd[k][0].right;
+                if (kRun > 1 && ref[k] >= cp[k]) {
+                    // children come after their parent: one pass over the run follows the walk through it
+                    int32_t to[kRun];
+#pragma unroll
+                    for (int i = 1; i < kRun; i++)
+                        to[i] = (tr.x(rowk[k], nd[k][i].feat) <= nd[k][i].thr) ? nd[k][i].left : nd[k][i].right;
+#pragma unroll
+                    for (int i = 1; i < kRun; i++) nr = nr == ref[k] + i ? to[i] : nr;
+                }
                 if (nr < 0) {
                     tr.vote(rowk[k], -nr - 1);
                     nr = kDone;
@@ -1666,15 +1690,24 @@ int resolve_job(const fp_packed* p, const fp_tune* t, const float* X, int64_t n_
     const bool blocks = h.layout >= FP_LAYOUT_BLOCKED;
     const bool auto_R = t->rows_per_block <= 0;
     if (t->rows_per_block > 4096) return fp_set_error(FP_EINVAL, "rows_per_block %d exceeds 4096", t->rows_per_block);
-    // tree_groups 0: one; for a block layout of at least 512 trees and 2^18
-    // walks launched alone (cus > 0), a group per 128 trees: a workgroup's LDS then holds several
-    // blocks of each of its trees instead of one or none (4,096 rows x 1,024
-    // trees: one group 60 us at its best tile, eight 47; 40,000 rows: 382 and
-    // 337), which pays for zeroing the votes and the classes' own launch
-    int G = t->tree_groups > 0                                                             ? t->tree_groups
-            : blocks && cus > 0 && h.n_trees >= 512 && n_rows * h.n_trees >= (1 << 18) && t->tree_passes <= 1 ? h.n_trees / 128
-                                                                                                   : 1;
-    if (t->tree_groups <= 0) G = std::min(G, 8);
+    // tree_groups 0: one, except for launches of their own (cus > 0) of at
+    // least 2^18 walks, which pay for zeroing the votes and the classes' own
+    // launch:
+    //  - block layouts of 512 trees or more: a group per 128 trees, so that a
+    //    workgroup's LDS holds several blocks of each of its trees instead of
+    //    one or none (4,096 rows x 1,024 trees: one group 60 us at its best
+    //    tile, eight 47; 40,000 rows: 382 and 337);
+    //  - node layouts larger than an XCD's L2 (4 MB): up to 8 groups, which
+    //    workgroup numbers spread over the XCDs, so that each L2 sees only its
+    //    groups' nodes (100,003 rows x 64 trees, 20 MB: one group 285 us at
+    //    its best tile, four 214), unless staging every row once per group
+    //    costs more (10,000 image rows x 128 trees: one 62 us, eight 76)
+    int G = std::max(1, t->tree_groups);
+    if (t->tree_groups <= 0 && cus > 0 && t->tree_passes <= 1 && n_rows * h.n_trees >= (1 << 18)) {
+        const int bins8 = std::min(8, h.n_bins);
+        if (blocks) G = std::max(1, h.n_trees >= 512 ? std::min(8, h.n_trees / 128) : 1);
+        else if (h.total_bytes > (int64_t(4) << 20) && (int64_t)h.n_features * bins8 <= 4 * (int64_t)h.n_trees) G = bins8;
+    }
     if (G > h.n_bins) G = h.n_bins;
     int P = t->tree_passes > 0 ? t->tree_passes : 1;
     if ((int64_t)P * G > h.n_bins) P = std::max(1, h.n_bins / G);
@@ -1682,22 +1715,23 @@ int resolve_job(const fp_packed* p, const fp_tune* t, const float* X, int64_t n_
     // passes that would hold no bin are dropped: the last pass writes the classes
     P = ((h.n_bins + bpg - 1) / bpg + G - 1) / G;
     const int tpg = (int)std::min<int64_t>((int64_t)bpg * h.bin_size, h.n_trees);
-    // rows_per_block 0: 16; a block layout launched alone: a tile per CU (with tree groups, per
-    // half CU and group), of at most 16,384 walks and 512 rows.  Fewer, larger
+    // rows_per_block 0, alone on the device: a tile per CU.  Fewer, larger
     // tiles leave CUs idle (300 image rows x 128 trees: 16-row tiles 15.9 us,
-    // 2-row ones 10.8); smaller ones stage the trees' first blocks and wait
-    // for their last walks more often (4,096 rows x 1,024 trees: 8-row tiles
-    // 71 us, 16-row ones 60; 10^6 rows x 32 trees: 16-row tiles 558 us,
-    // 128-row ones 270, 512-row ones 241)
-    const int64_t most = std::min<int64_t>(512, std::max<int64_t>(32, 16384 / tpg));
-    // A job of a plan shares the device: 16 to 64 rows, 64 tiles or more (16
+    // 2-row ones 10.8); smaller ones stage the trees' tops and wait for their
+    // last walks more often (4,096 rows x 1,024 trees: 8-row tiles 71 us,
+    // 16-row ones 60; 10^6 rows x 32 trees: 16-row tiles 558 us, 128-row ones
+    // 270, 512-row ones 241).  At most 16,384 walks and 512 rows for blocks,
+    // 256 rows for nodes; with tree groups two (nodes: five) workgroups a CU.
+    // A plan's jobs share the device: 16 to 64 rows, 64 tiles or more (16
     // forests of up to 512 trees and 60,000 rows: 16-row tiles 488 us, 32-row
-    // ones 393, 64-row ones 333; 8 forests, 10,000 rows: 78, 58 and 58)
-    int R = !auto_R               ? t->rows_per_block
-            : !blocks || cus < 0 ? 16
-            : cus == 0           ? (int)std::min<int64_t>(64, std::max<int64_t>(16, n_rows / 64))
-            : G > 1   ? (int)std::min(most, std::max<int64_t>(16, (n_rows * G + 2 * cus - 1) / (2 * cus)))
-                      : (int)std::min(most, std::max<int64_t>(1, (n_rows + cus - 1) / cus));
+    // ones 393, 64-row ones 333; 8 forests, 10,000 rows: 78, 58 and 58).
+    // Node layouts there, and serving, take 16.
+    const int64_t most = blocks ? std::min<int64_t>(512, std::max<int64_t>(32, 16384 / tpg)) : 256;
+    const int64_t per_cu = G == 1 ? 1 : blocks ? 2 : 5;
+    int R = !auto_R    ? t->rows_per_block
+            : cus > 0  ? (int)std::min(most, std::max<int64_t>(G > 1 ? 16 : 1, (n_rows * G + per_cu * cus - 1) / (per_cu * cus)))
+            : cus == 0 && blocks ? (int)std::min<int64_t>(64, std::max<int64_t>(16, n_rows / 64))
+                       : 16;
     if ((int64_t)R * tpg >= (1 << 30)) return fp_set_error(FP_E2BIG, "rows_per_block x trees per group too large");
     const uint8_t* base = static_cast<const uint8_t*>(p->dev);
     memset(j, 0, sizeof *j);
@@ -1715,6 +1749,7 @@ int resolve_job(const fp_packed* p, const fp_tune* t, const float* X, int64_t n_
     j->C = h.n_classes;
     j->n_bins = h.n_bins;
     j->n_trees = h.n_trees;
+    j->n_nodes = (int32_t)h.n_nodes;
     j->bin_size = h.bin_size;
     j->R = R;
     j->G = G;
@@ -1752,10 +1787,17 @@ int resolve_job(const fp_packed* p, const fp_tune* t, const float* X, int64_t n_
         j->stage_rows = feat && ld % 4 == 0 && reinterpret_cast<uintptr_t>(X) % 16 == 0 && h.n_features <= 4096;
         return job_lds_layout(j);
     };
+    // An automatic tile of a node layout shares a CU with three others of 512
+    // threads: half of the LDS that a block layout's 1024 threads take
+    if (auto_R && !blocks && cus > 0 && size_for(1, t->feature_lds >= 0) <= lds_block / 2) lds_block /= 2;
     // fit by shrinking an automatic tile first (features in LDS matter most),
     // then by reading features from memory.  An automatic tile leaves LDS for
-    // a block per tree, up to an eighth of the budget
-    const size_t tops = auto_R && blocks ? std::min(lds_block / 8, (size_t)tpg * (size_t)j->block_bytes) : 0;
+    // a block per tree, up to an eighth of the budget, or for half of the
+    // bins' top nodes
+    const size_t tops = !auto_R                         ? 0
+                        : blocks                        ? std::min(lds_block / 8, (size_t)tpg * (size_t)j->block_bytes)
+                        : h.layout == FP_LAYOUT_COMPACT ? 0
+                        : cus > 0 ? std::min(lds_block / 2, (size_t)bpg * (size_t)h.max_top_len * sizeof(Node16)) : 0;
     auto fit = [&](bool feat) {
         size_t need = size_for(R, feat);
         if (!auto_R || need + (feat ? tops : 0) <= lds_block) return need;
@@ -1974,8 +2016,12 @@ static int predict_impl(const fp_packed* p, const fp_tune* tune, const float* X,
     hipStream_t stream = static_cast<hipStream_t>(stream_v);
     // block layouts: 16 waves a workgroup, which share its tile and first
     // blocks (20,001 rows x 784 features x 256 trees, 16-row tiles: 256
-    // threads 142 us, 1024 threads 102)
-    const int threads = tune && tune->block_threads > 0 ? tune->block_threads : h.layout >= FP_LAYOUT_BLOCKED ? 1024 : 256;
+    // threads 142 us, 1024 threads 102); node layouts 8 (2,000 rows x 64
+    // trees, 8-row tiles: 256 threads 21 us, 512 threads 15)
+    const int threads = tune && tune->block_threads > 0   ? tune->block_threads
+                        : h.layout >= FP_LAYOUT_BLOCKED   ? 1024
+                        : h.layout == FP_LAYOUT_NAIVE     ? 256
+                                                          : 512;
     if (threads % 64 || threads < 64 || threads > 1024)
         return fp_set_error(FP_EINVAL, "block_threads %d must be a multiple of 64 in [64, 1024]", threads);
 
@@ -1994,7 +2040,9 @@ static int predict_impl(const fp_packed* p, const fp_tune* tune, const float* X,
         return check_launch("naive_kernel");
     }
 
-    const int K = tune && tune->cursors > 0 ? tune->cursors : 2;
+    // one walk per lane: more cost registers and gain nothing (100,003 rows x
+    // 64 trees: one 214 us, two 227)
+    const int K = tune && tune->cursors > 0 ? tune->cursors : 1;
     if (K != 1 && K != 2 && K != 4 && K != 8) return fp_set_error(FP_EINVAL, "cursors must be 1, 2, 4 or 8");
     const size_t lds_max = dp.lds_per_block ? dp.lds_per_block : 65536;
     if (tune && tune->lds_bytes < 0) return fp_set_error(FP_EINVAL, "lds_bytes %d < 0", tune->lds_bytes);
