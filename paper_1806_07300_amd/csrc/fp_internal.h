@@ -240,7 +240,8 @@ inline int32_t walk_form(const Header& h) {
     if (h.layout == FP_LAYOUT_CLUSTERED && h.block_bytes == 48)
         return h.n_classes <= 16 && section / 32 < (1 << 20) - kGlobalRef ? kWalk32h : kWalk48h;
     if (h.layout != FP_LAYOUT_CLUSTERED && h.layout != FP_LAYOUT_BLOCKED) return kWalkNone;
-    if (h.block_bytes == 48) return h.n_classes <= 32 && h.n_used_features <= 1024 ? kWalk48b : kWalkNone;
+    if (h.layout == FP_LAYOUT_BLOCKED && h.n_classes <= 32 && h.n_used_features <= 1024) return kWalk48b;
+    if (h.block_bytes == 48) return kWalkNone;
     if (h.n_classes <= 8 && h.n_used_features <= 1024) return kWalk48f;
     return h.n_classes <= 128 && h.n_used_features <= 65535 ? kWalk64 : kWalkNone;
 }
