@@ -5,12 +5,13 @@ ones are its extra keys."""
 
 IMAGE = {
     "pack": {"layout": 4, "bin_size": 128, "interleave_depth": 3, "line_align": 0},
-    # 104 rows of 353 used features, staged as fp16 (every threshold of this
+    # 96 rows of 353 used features, staged as fp16 (every threshold of this
     # forest is exact in fp16), fill the LDS share of one of two workgroups
-    # per CU but for some of the trees' 32-byte root blocks (96 rows with all
-    # of them are 1.5% slower); feature_lds 1 turns a tile that no longer fits
-    # into an error instead of a silent fall back to features read from memory
-    "tune": {"rows_per_block": 104, "cursors": 1, "tree_groups": 1, "block_threads": 1024, "refill_lanes": 24,
+    # per CU but for 139 blocks: the 128 trees' root blocks are served from
+    # LDS (104 rows fit too, as fast, with no blocks in LDS); feature_lds 1
+    # turns a tile that no longer fits into an error instead of a silent fall
+    # back to features read from memory
+    "tune": {"rows_per_block": 96, "cursors": 1, "tree_groups": 1, "block_threads": 1024, "refill_lanes": 48,
              "feature_lds": 1},
     "naive_tune": {"block_threads": 256},
 }
@@ -28,7 +29,7 @@ IMAGE = {
 # workgroups per CU 345 ms; this launch 269 ms
 TABULAR = {
     "pack": {"layout": 4, "bin_size": 16, "interleave_depth": 3, "line_align": 0},
-    "tune": {"rows_per_block": 768, "cursors": 1, "tree_groups": 1, "block_threads": 1024, "refill_lanes": 48,
+    "tune": {"rows_per_block": 768, "cursors": 1, "tree_groups": 1, "block_threads": 1024, "refill_lanes": 24,
              "feature_lds": 1, "tree_passes": 16, "lds_bytes": 163840},
     "naive_tune": {"block_threads": 256},
 }
