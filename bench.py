@@ -577,7 +577,8 @@ def vmem_ceiling(fp, torch, res, fetch_bytes):
     holds it) with 4 or 8 chains per lane.  The kernel's count is the
     training-distributed fetches per walk from the packed header times the
     walks of a step; blocks served from LDS are included, so the fraction is
-    an upper estimate."""
+    an upper estimate.  fetch_bytes: a block in its walk form on the device,
+    or the largest size the probe has below it."""
     g = gather_ceiling(fp, torch, 16 << 10, fetch_bytes, chains=(4, 8))
     walks = res["n_rows"] * res["n_trees"]
     kernel = res["expected_fetches_per_walk"] * walks / (res["ms_per_step"] / 1e3)
@@ -671,10 +672,10 @@ def headline(args, fp, torch, np, presets, tab_w):
     forest, packed, naive, Xd, votes, cls = res.pop("_keep")
     del naive, Xd, votes, cls
     torch.cuda.empty_cache()
-    res["block_bytes_per_fetch"] = 64
+    res["block_bytes_per_fetch"] = 48
     rl = roofline(res, "tabular")
-    vm = vmem_ceiling(fp, torch, res, 64)
-    log(f"vector-memory ceiling: {vm['probe_block_fetches_per_s'] / 1e9:.0f} G 64-byte blocks/s (L1-resident probe); "
+    vm = vmem_ceiling(fp, torch, res, 48)
+    log(f"vector-memory ceiling: {vm['probe_block_fetches_per_s'] / 1e9:.0f} G 48-byte blocks/s (L1-resident probe); "
         f"kernel {vm['kernel_block_fetches_per_s'] / 1e9:.0f} G/s = {vm['frac']:.2f}")
     out = {
         "metric": METRIC,
@@ -784,11 +785,11 @@ def main():
         elif leg == "image":
             r = single_forest_leg("image", img_w, presets.IMAGE, args, fp, torch, np, 20, 3, 3)
             image_forest = r.pop("_keep")[0]
-            r["block_bytes_per_fetch"] = 48
+            r["block_bytes_per_fetch"] = 32
             r["compare"] = ("fp16: rows staged in LDS rounded toward +inf, every threshold exact in fp16 "
-                            "(48-byte clustered blocks); decides every x <= t exactly as fp32")
+                            "(48-byte clustered blocks, 32 bytes on the device); decides every x <= t exactly as fp32")
             r["roofline"] = roofline(r, "image")
-            r["vmem_ceiling"] = vmem_ceiling(fp, torch, r, 48)
+            r["vmem_ceiling"] = vmem_ceiling(fp, torch, r, 16)
             torch.cuda.empty_cache()
         elif leg == "batched":
             r = leg_batched(args, fp, synth, torch, np, 8 if args.lite else 64)

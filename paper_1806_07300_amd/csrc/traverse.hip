@@ -28,8 +28,10 @@
 // Split test everywhere: x <= threshold in fp32 (v_cmp_le_f32; NaN -> right).
 // The CLUSTERED 48-byte form, whose thresholds are all exact in fp16, stages
 // the tile as fp16 values rounded toward +infinity and compares in fp16
-// (v_cmp_le_f16), which decides every test exactly as the fp32 compare: for
+// (v_cmpx_nle_f16), which decides every test exactly as the fp32 compare: for
 // t exact in fp16, x <= t exactly when the smallest fp16 value >= x is <= t.
+// Blocks are walked in a form of their own, made when a forest is uploaded
+// (WalkForm in fp_internal.h, walk_form_kernel).
 // Built without fast-math and without denormal flushing.
 #include <hip/hip_runtime.h>
 
