@@ -587,6 +587,7 @@ __device__ __forceinline__ void run_tile(const JobDesc& j, int nt, int tile, uns
     const int U = rows_here * nt;
     const uint32_t rmagic = 0xFFFFFFFFu / (uint32_t)rows_here;
     TileRows tr{j, xs, vl, fmap_l, row0, feat_lds};
+    const uint32_t f_max = (uint32_t)(j.Fc - 1);
     // per cursor: row in the tile, gb = bin base in the node array, lb = the
     // bin's first top node in LDS, cp = top nodes staged in LDS
     int32_t ref[K], rowk[K], gb[K], lb[K], cp[K];
@@ -627,11 +628,14 @@ __device__ __forceinline__ void run_tile(const JobDesc& j, int nt, int tile, uns
             if (ref[k] >= 0) {
                 int32_t nr = (tr.x(rowk[k], nd[k][0].feat) <= nd[k][0].thr) ? nd[k][0].left : nd[k][0].right;
                 if (kRun > 1 && ref[k] >= cp[k]) {
-                    // children come after their parent: one pass over the run follows the walk through it
+                    // children come after their parent: one pass over the run follows the walk through it.
+                    // A node that the walk does not reach may be a gap behind a bin, whose content the
+                    // verifier does not look at: its feature is held inside the row
                     int32_t to[kRun];
 #pragma unroll
                     for (int i = 1; i < kRun; i++)
-                        to[i] = (tr.x(rowk[k], nd[k][i].feat) <= nd[k][i].thr) ? nd[k][i].left : nd[k][i].right;
+                        to[i] = (tr.x(rowk[k], (int32_t)min((uint32_t)nd[k][i].feat, f_max)) <= nd[k][i].thr) ? nd[k][i].left
+                                                                                                           : nd[k][i].right;
 #pragma unroll
                     for (int i = 1; i < kRun; i++) nr = nr == ref[k] + i ? to[i] : nr;
                 }
