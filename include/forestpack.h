@@ -462,7 +462,9 @@ int fp_autotune(const fp_forest_view *forest, const float *X_dev, int64_t n_rows
  * persistent kernel whose workgroups pull (forest, tree group, row tiles)
  * work items from a device counter, largest estimated cost first (cost =
  * rows x trees x expected depth, the cost model of Eqs. 1-2).  The launch is
- * captured once in a hipGraph (counter reset, vote zeroing, kernel, argmax)
+ * captured once in a hipGraph (a kernel for the jobs in block layouts and one
+ * for those in node layouts, with vote zeroing before and argmax after them
+ * only where tree groups share rows; the counters wrap to zero by themselves)
  * and replayed by fp_predict_batched.
  *
  * fp_job: one forest (uploaded, packed layout) with its rows.  Pointers are
@@ -516,7 +518,9 @@ typedef struct fp_plan_info {
  * device), FP_E2BIG (LDS), FP_ENOMEM, FP_EHIP. */
 int fp_plan_create(const fp_job *jobs, int32_t n_jobs, const fp_plan_opts *opts, fp_plan **out);
 
-/* Run every job of the plan on `stream` (graph replay or plain launches). */
+/* Run every job of the plan on `stream` (graph replay or plain launches).
+ * Runs of one plan write the same votes: order them (one stream, or events).
+ * Runs that overlap all the same leave nothing behind: the next run is whole. */
 int fp_predict_batched(fp_plan *plan, void *stream);
 
 int fp_plan_info_get(const fp_plan *plan, fp_plan_info *out);
@@ -527,8 +531,8 @@ void fp_plan_free(fp_plan *plan);
  * For callers that cannot allocate device memory (code under HIP graph
  * capture, tight serving loops, harnesses that forbid hipMalloc): one batched
  * run of `jobs` -- what fp_plan_create followed by fp_predict_batched computes,
- * with the same kernels -- that allocates nothing.  The job table, the work
- * list and the work counter go to a fixed device array of 1 MiB inside the
+ * with the same kernels -- that allocates nothing.  The work counters, the job
+ * table and the work list go to a fixed device array of 1 MiB inside the
  * library (one per GPU, held until the process ends), filled by a copy from
  * a static host area that HIP performs synchronously; no hipMalloc, hipFree
  * or other allocating call is made.  Limits: at most 4,096 jobs and as many
@@ -538,8 +542,9 @@ void fp_plan_free(fp_plan *plan);
  * own tune; opts->autotune must be 0 (FP_EINVAL), use_graph is ignored.
  * Calls on one GPU share its array: a call waits for earlier work on
  * `stream` before overwriting it, but calls that overlap on different
- * streams of one GPU race.  Arguments, ownership and other errors are those
- * of fp_plan_create and fp_predict_batched.
+ * streams of one GPU race (a later call does not suffer from it).  Arguments,
+ * ownership and other errors are those of fp_plan_create and
+ * fp_predict_batched.
  */
 int fp_predict_batched_noalloc(const fp_job *jobs, int32_t n_jobs, const fp_plan_opts *opts, void *stream);
 

@@ -379,7 +379,8 @@ int launch_argmax(const int32_t* votes, int32_t* cls, int64_t n, int32_t C, hipS
 int launch_packed(const JobDesc& j, int K, int threads, int blocks, hipStream_t s);
 // Zeroes the votes of jobs that accumulate with atomics, walks the work list
 // and takes their classes; kernels without work are left out.  `counters`: two
-// zeros in device memory, zero again when the launch ends.
+// zeros in device memory, zero again when the launch, and whatever launch of
+// the same list overlaps it, has ended.
 int launch_batched(const BatchedShape& sh, const JobDesc* jobs, const WorkItem* items, int32_t n_block_items, int32_t n_items,
                    int32_t* counters, hipStream_t s);
 

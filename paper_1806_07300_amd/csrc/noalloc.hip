@@ -1,8 +1,10 @@
 // Batched prediction that allocates nothing: for callers that cannot
 // allocate device memory (code under HIP graph capture, tight serving
-// loops).  The job table, the work list and the work counter that
+// loops).  The work counters, the job table and the work list that
 // fp_plan_create allocates for a plan live here in a file-scope device
 // array of kScratchBytes, one copy per device, held until the process ends.
+// Each call copies all three, so it starts from zero counters whatever ran
+// before it.
 // The kernels are the batched path's; only where their tables live differs.
 #include <hip/hip_runtime.h>
 
@@ -14,7 +16,8 @@
 
 namespace {
 
-constexpr size_t kScratchBytes = size_t(1) << 20;  // job table + work items + counter
+constexpr size_t kScratchBytes = size_t(1) << 20;  // counters + job table + work items
+constexpr size_t kCounterBytes = 256;              // at its start
 constexpr int kMaxDevices = 64;
 constexpr int32_t kMaxJobs = 4096;
 
@@ -76,7 +79,7 @@ extern "C" int fp_predict_batched_noalloc(const fp_job* jobs, int32_t n_jobs, co
     // job descriptors, built in the static host image (no allocation): each
     // job's launch parameters are its forest's (or a recorded tune for the
     // plan's workgroup size and cursors)
-    fp::JobDesc* jd = reinterpret_cast<fp::JobDesc*>(g_host);
+    fp::JobDesc* jd = reinterpret_cast<fp::JobDesc*>(g_host + kCounterBytes);
     for (int32_t i = 0; i < n_jobs; i++) {
         const fp_job& jb = jobs[i];
         if (!jb.forest) return fp_set_error(FP_EINVAL, "job %d: forest is NULL", i);
@@ -98,8 +101,8 @@ extern "C" int fp_predict_batched_noalloc(const fp_job* jobs, int32_t n_jobs, co
     if (rc) return rc;
     // the plan's work list, written straight after the job table
     for (int32_t i = 0; i < n_jobs; i++) g_depth[i] = jobs[i].forest->hdr.expected_depth;
-    fp::WorkItem* items = reinterpret_cast<fp::WorkItem*>(g_host + jobs_bytes);
-    const size_t max_items = (kScratchBytes - jobs_bytes - 256) / sizeof(fp::WorkItem);
+    fp::WorkItem* items = reinterpret_cast<fp::WorkItem*>(g_host + kCounterBytes + jobs_bytes);
+    const size_t max_items = (kScratchBytes - kCounterBytes - jobs_bytes) / sizeof(fp::WorkItem);
     double cost = 0.0;
     int32_t n_block_items = 0;
     size_t n_items = fp::build_items_into(jd, g_depth, (size_t)n_jobs, shape, ipb, items, max_items, &n_block_items, &cost);
@@ -109,15 +112,16 @@ extern "C" int fp_predict_batched_noalloc(const fp_job* jobs, int32_t n_jobs, co
     if (n_items > max_items)
         return fp_set_error(FP_E2BIG, "%zu work items exceed the scratch's %zu", n_items, max_items);
     uint8_t* base = static_cast<uint8_t*>(sp);
-    const size_t table_bytes = jobs_bytes + n_items * sizeof(fp::WorkItem);
-    int32_t* counters = reinterpret_cast<int32_t*>(base + kScratchBytes - 256);  // zero at load and after each launch
+    const size_t table_bytes = kCounterBytes + jobs_bytes + n_items * sizeof(fp::WorkItem);
+    memset(g_host, 0, kCounterBytes);
     // g_host is pageable, so HIP performs this copy synchronously (its
     // documented behaviour for unpinned memory): g_host may be rebuilt as
     // soon as the call returns; the copy is ordered after earlier work on
     // `stream`
     const hipError_t e = hipMemcpyAsync(base, g_host, table_bytes, hipMemcpyHostToDevice, stream);
     if (e != hipSuccess) return fp_set_error(FP_EHIP, "hipMemcpyAsync (tables): %s", hipGetErrorString(e));
-    const fp::JobDesc* jobs_dev = reinterpret_cast<const fp::JobDesc*>(base);
-    const fp::WorkItem* items_dev = reinterpret_cast<const fp::WorkItem*>(base + jobs_bytes);
-    return fp::launch_batched(shape, jobs_dev, items_dev, n_block_items, (int32_t)n_items, counters, stream);
+    const fp::JobDesc* jobs_dev = reinterpret_cast<const fp::JobDesc*>(base + kCounterBytes);
+    const fp::WorkItem* items_dev = reinterpret_cast<const fp::WorkItem*>(base + kCounterBytes + jobs_bytes);
+    return fp::launch_batched(shape, jobs_dev, items_dev, n_block_items, (int32_t)n_items, reinterpret_cast<int32_t*>(base),
+                              stream);
 }

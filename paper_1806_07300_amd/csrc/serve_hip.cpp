@@ -17,7 +17,7 @@
 namespace {
 
 constexpr size_t kAlign = 256;
-constexpr size_t kTableBytes = 4u << 20;  // per slot: job table + work items
+constexpr size_t kTableBytes = 4u << 20;  // per slot: work counters (kAlign bytes) + job table + work items
 
 size_t align_up(size_t v) { return (v + kAlign - 1) / kAlign * kAlign; }
 
@@ -97,9 +97,7 @@ class HipExecutor final : public fp::ServeExecutor {
             e = hipMalloc(&sl.d_tables, kTableBytes);
             if (e == hipSuccess) e = hipHostMalloc(&sl.h_tables, kTableBytes, hipHostMallocDefault);
             if (e != hipSuccess) return fp_set_error(FP_ENOMEM, "slot tables: %s", hipGetErrorString(e));
-            const int32_t zeros[2] = {0, 0};  // the work counters
-            e = hipMemcpy(static_cast<uint8_t*>(sl.d_tables) + kTableBytes - kAlign, zeros, sizeof zeros, hipMemcpyHostToDevice);
-            if (e != hipSuccess) return fp_set_error(FP_EHIP, "slot tables: %s", hipGetErrorString(e));
+            memset(sl.h_tables, 0, kAlign);  // the work counters, copied with every launch's tables
         }
         return FP_OK;
     }
@@ -143,11 +141,12 @@ class HipExecutor final : public fp::ServeExecutor {
             if (jobs_bytes + items.size() * sizeof(fp::WorkItem) + kAlign <= kTableBytes) break;
             if (ipb == 1) return fp_set_error(FP_E2BIG, "launch tables exceed %zu bytes", kTableBytes);
         }
-        memcpy(s.h_tables, jobs.data(), jobs.size() * sizeof(fp::JobDesc));
-        memcpy(static_cast<uint8_t*>(s.h_tables) + jobs_bytes, items.data(), items.size() * sizeof(fp::WorkItem));
+        uint8_t* ht = static_cast<uint8_t*>(s.h_tables);
+        memcpy(ht + kAlign, jobs.data(), jobs.size() * sizeof(fp::JobDesc));
+        memcpy(ht + kAlign + jobs_bytes, items.data(), items.size() * sizeof(fp::WorkItem));
         uint8_t* dt = static_cast<uint8_t*>(s.d_tables);
-        int32_t* counters = reinterpret_cast<int32_t*>(dt + kTableBytes - kAlign);
-        hipError_t e = hipMemcpyAsync(dt, s.h_tables, jobs_bytes + items.size() * sizeof(fp::WorkItem),
+        int32_t* counters = reinterpret_cast<int32_t*>(dt);
+        hipError_t e = hipMemcpyAsync(dt, ht, kAlign + jobs_bytes + items.size() * sizeof(fp::WorkItem),
                                       hipMemcpyHostToDevice, s.stream);
         // rows: one copy per run of adjacent ring blocks
         for (size_t i = 0; i < batch.size() && e == hipSuccess;) {
@@ -161,8 +160,8 @@ class HipExecutor final : public fp::ServeExecutor {
             (void)hipStreamSynchronize(s.stream);
             return fp_set_error(FP_EHIP, "hipMemcpyAsync: %s", hipGetErrorString(e));
         }
-        const fp::JobDesc* jobs_dev = reinterpret_cast<const fp::JobDesc*>(dt);
-        const fp::WorkItem* items_dev = reinterpret_cast<const fp::WorkItem*>(dt + jobs_bytes);
+        const fp::JobDesc* jobs_dev = reinterpret_cast<const fp::JobDesc*>(dt + kAlign);
+        const fp::WorkItem* items_dev = reinterpret_cast<const fp::WorkItem*>(dt + kAlign + jobs_bytes);
         rc = fp::launch_batched(shape, jobs_dev, items_dev, n_block_items, (int32_t)items.size(), counters, s.stream);
         if (rc) {
             (void)hipStreamSynchronize(s.stream);

@@ -1506,9 +1506,11 @@ __device__ __forceinline__ void item_tiles(const JobDesc& j, const WorkItem& w, 
 // The item number is broadcast through a slot at the end of the dynamic LDS
 // (item_slot bytes in), not a static __shared__ variable: static LDS would
 // add to every job's budget and leave two workgroups no longer fitting a CU.
-// Every workgroup draws one number past the list; the last of them, which
-// draws n_items + gridDim.x - 1, sets the counter back to 0 for the next
-// launch, so no kernel has to clear it first.
+// The counter wraps to 0 after n_items + gridDim.x draws, which is what a
+// launch makes (each workgroup draws one number past the list), so no kernel
+// has to clear it first.  Launches of one list that overlap share the draws:
+// each number past the list still ends one workgroup, so together they make
+// whole rounds of the counter, walk every item once per launch and leave 0.
 template <int K, bool BLOCKS>
 __global__ __launch_bounds__(1024, (BLOCKS || K <= 2 ? 8 : 4)) void batched_kernel(const JobDesc* __restrict__ jobs,
                                                                                    const WorkItem* __restrict__ items,
@@ -1518,17 +1520,15 @@ __global__ __launch_bounds__(1024, (BLOCKS || K <= 2 ? 8 : 4)) void batched_kern
     int32_t* s_item = reinterpret_cast<int32_t*>(smem + item_slot);
     int staged_job = -1, staged_group = -1, nt = 0;
     while (true) {
-        if (threadIdx.x == 0) *s_item = atomicAdd(counter, 1);
+        if (threadIdx.x == 0)
+            *s_item = (int32_t)atomicInc(reinterpret_cast<unsigned*>(counter), (unsigned)n_items + gridDim.x - 1);
         __syncthreads();
         // the item is the workgroup's: readfirstlane makes that visible to the
         // compiler, so the item and its job descriptor are loaded into scalar
         // registers instead of occupying vector registers in every lane
         const int it = __builtin_amdgcn_readfirstlane(*s_item);
         __syncthreads();
-        if (it >= n_items) {
-            if (threadIdx.x == 0 && it == n_items + (int)gridDim.x - 1) atomicExch(counter, 0);
-            break;
-        }
+        if (it >= n_items) break;
         const WorkItem w = items[it];
         const JobDesc& j = jobs[w.job];
         if (w.job != staged_job || w.group != staged_group) {
