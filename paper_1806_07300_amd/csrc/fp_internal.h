@@ -279,7 +279,7 @@ struct JobDesc {
     int32_t n_tiles;
     int32_t atomic_votes;      // several tree groups add into the same votes
     int32_t feat_lds;          // 1: observation tile in LDS, 0: read from memory
-    int32_t off_top, off_ttab, off_fmap, off_xs, off_votes, off_pool, lds_bytes;
+    int32_t off_ttab, off_fmap, off_xs, off_votes, off_pool, lds_bytes;  // the bin tops come first, at 0
     int32_t layout;            // FP_LAYOUT_PACKED, FP_LAYOUT_COMPACT or FP_LAYOUT_BLOCKED
     int32_t fbits, cbits;      // COMPACT / BLOCKED field widths
     int32_t refill_min;        // idle lanes of a wavefront that trigger a refill
@@ -295,6 +295,7 @@ struct JobDesc {
     int32_t n_trees;
     int32_t n_nodes;           // entries of the node section
 };
+static_assert(sizeof(JobDesc) == 208, "the no-alloc scratch holds 4,096 jobs and 12,272 items of them");
 
 // A job whose groups run in several passes, flattened for launches where all
 // groups run concurrently (batched plans, the server): every group of every

@@ -486,7 +486,7 @@ __device__ __forceinline__ int stage_group(const JobDesc& j, int group, unsigned
     const int b_lo = group * j.bins_per_group;
     const int b_hi = min(b_lo + j.bins_per_group, j.n_bins);
     if (b_lo >= b_hi) return 0;
-    uint4* top = reinterpret_cast<uint4*>(smem + j.off_top);
+    uint4* top = reinterpret_cast<uint4*>(smem);
     int4* ttab = reinterpret_cast<int4*>(smem + j.off_ttab);
     const int t_lo = b_lo * j.bin_size;
     const int nt = (int)min((int64_t)b_hi * j.bin_size, (int64_t)j.n_trees) - t_lo;
@@ -573,7 +573,7 @@ template <int K, int FMODE>
 __device__ __forceinline__ void run_tile(const JobDesc& j, int nt, int tile, unsigned char* smem) {
     constexpr int kRun = K <= 2 ? 2 : 1;
     const bool feat_lds = FMODE == 2 ? (j.feat_lds != 0) : (FMODE == 1);
-    const Node16* top = reinterpret_cast<const Node16*>(smem + j.off_top);
+    const Node16* top = reinterpret_cast<const Node16*>(smem);
     const int4* ttab = reinterpret_cast<const int4*>(smem + j.off_ttab);
     const int32_t* fmap_l = reinterpret_cast<const int32_t*>(smem + j.off_fmap);
     float* xs = reinterpret_cast<float*>(smem + j.off_xs);
@@ -849,7 +849,7 @@ __device__ __forceinline__ void run_tile_blocked(const JobDesc& j, int nt, int t
         const float x = feat_lds ? lds_ptr<float>((uint32_t)xrow)[f] : j.X[(row0 + xrow) * j.ld + fmap_l[f]];
         return x <= thr;
     };
-    const uint32_t xs_addr = lds_addr(xs), blocks_addr = lds_addr(smem + j.off_top);
+    const uint32_t xs_addr = lds_addr(xs), blocks_addr = lds_addr(smem);
     // the block an exit leaves to: rank from the code (48-byte form) or the table
     auto exit_to = [&](const BlockView& b, uint32_t e, uint32_t code) -> int32_t {
         const uint32_t rank = B48 ? (code >> 1) : ((b.ranks >> (4 * e)) & 7u);
@@ -1668,8 +1668,7 @@ size_t default_lds_block(const DeviceProps& dp) {
 }
 
 size_t job_lds_layout(JobDesc* j) {
-    size_t o = 0;
-    j->off_top = (int32_t)o;   o += (size_t)j->cap * j->bins_per_group * sizeof(Node16);
+    size_t o = (size_t)j->cap * j->bins_per_group * sizeof(Node16);
     j->off_ttab = (int32_t)o;  o += round16((size_t)j->trees_per_group * (j->form != kWalkNone ? 4 : 16));
     j->off_fmap = (int32_t)o;  o += j->feat_lds ? 0 : round16((size_t)j->Fc * 4);
     j->off_imap = (int32_t)o;  o += j->stage_rows ? round16((size_t)(j->F + 3) / 4 * 4 * 2) : 0;
