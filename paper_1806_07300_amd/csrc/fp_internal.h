@@ -402,7 +402,8 @@ int search_launch(const fp_packed* p, const float* X, int64_t n_rows, int64_t ld
 // Work list of a batched launch (plan.cpp): chunks of row tiles per (job,
 // tree group), about `items_per_block` items per resident workgroup, block
 // layouts first, in each class largest estimated cost first.
-// `expected_depth[i]` is job i's forest cost model.
+// `expected_depth[i]` is job i's forest cost model.  items_per_block 0: one
+// item per (job, tree group), the shortest list there is.
 void build_items(const std::vector<JobDesc>& jobs, const std::vector<double>& expected_depth, const BatchedShape& sh,
                  int items_per_block, std::vector<WorkItem>* items, int32_t* n_block_items, double* total_cost);
 // The same into caller memory of cap items; returns the number of items

@@ -106,9 +106,13 @@ extern "C" int fp_predict_batched_noalloc(const fp_job* jobs, int32_t n_jobs, co
     double cost = 0.0;
     int32_t n_block_items = 0;
     size_t n_items = fp::build_items_into(jd, g_depth, (size_t)n_jobs, shape, ipb, items, max_items, &n_block_items, &cost);
-    // jobs of both layout classes make up to twice the items of one list
-    if (n_items > max_items && shape.lds[0] && shape.lds[1] && ipb > 1)
-        n_items = fp::build_items_into(jd, g_depth, (size_t)n_jobs, shape, ipb / 2, items, max_items, &n_block_items, &cost);
+    // jobs of both layout classes make two lists, together up to twice as
+    // long as one: coarser items, down to one per (job, tree group), hold
+    // what one list would
+    for (int c = ipb; n_items > max_items && shape.lds[0] && shape.lds[1] && c > 0;) {
+        c /= 2;
+        n_items = fp::build_items_into(jd, g_depth, (size_t)n_jobs, shape, c, items, max_items, &n_block_items, &cost);
+    }
     if (n_items > max_items)
         return fp_set_error(FP_E2BIG, "%zu work items exceed the scratch's %zu", n_items, max_items);
     uint8_t* base = static_cast<uint8_t*>(sp);

@@ -65,7 +65,8 @@ size_t build_items_into(const JobDesc* jobs, const double* expected_depth, size_
     }
     size_t k = 0, k_block = 0;
     for (int c = 0; c < 2; c++) {
-        const double target = total[c] / (double)std::max<int64_t>(1, sh.resident[c] * std::max(1, items_per_block));
+        const double target = items_per_block > 0 ? total[c] / (double)std::max<int64_t>(1, sh.resident[c] * items_per_block)
+                                                  : HUGE_VAL;
         for (size_t i = 0; i < n; i++) {
             const JobDesc& j = jobs[i];
             if (batched_class(j) != c || j.n_rows == 0) continue;

@@ -139,7 +139,7 @@ class HipExecutor final : public fp::ServeExecutor {
         for (int ipb = 4;; ipb /= 2) {
             fp::build_items(jobs, depth, shape, ipb, &items, &n_block_items, &cost);
             if (jobs_bytes + items.size() * sizeof(fp::WorkItem) + kAlign <= kTableBytes) break;
-            if (ipb == 1) return fp_set_error(FP_E2BIG, "launch tables exceed %zu bytes", kTableBytes);
+            if (ipb == 0) return fp_set_error(FP_E2BIG, "launch tables exceed %zu bytes", kTableBytes);
         }
         uint8_t* ht = static_cast<uint8_t*>(s.h_tables);
         memcpy(ht + kAlign, jobs.data(), jobs.size() * sizeof(fp::JobDesc));

@@ -1,5 +1,7 @@
 """What the no-alloc call's fixed scratch has to hold: a full table of 4,096
-jobs with 11,092 work items.  Whole numbers: equal to the CPU checker's."""
+jobs with 11,092 work items, and the two work lists of block-layout and
+node-layout jobs where one list over both would fit.  Whole numbers: equal to
+the CPU checker's."""
 import numpy as np
 import pytest
 import torch
@@ -31,6 +33,20 @@ def test_full_job_table():
     torch.cuda.synchronize()
     want = oracle.predict(f, X)
     assert np.array_equal(votes.cpu().numpy(), want[0]) and np.array_equal(cls.cpu().numpy(), want[1])
+
+
+def test_lists_of_both_layout_classes():
+    """51,000 and 20,000 tiles; at 100 items a workgroup one list would chunk the cheap ones."""
+    jobs, want = [], []
+    for n, trees, layout in ((408_000, 20, fp.FP_LAYOUT_BLOCKED), (160_000, 6, fp.FP_LAYOUT_PACKED)):
+        f, p = packed(trees, layout, rows_per_block=8, tree_groups=1)
+        X = np.random.default_rng(n).random((n, 8), dtype=np.float32)
+        jobs.append((p, torch.from_numpy(X).cuda(), torch.full((n, 4), -7, dtype=torch.int32, device="cuda"), None))
+        want.append(oracle.predict(f, X)[0])
+    fp.fp_predict_batched_noalloc(jobs, items_per_block=100)
+    torch.cuda.synchronize()
+    for (_, _, votes, _), w in zip(jobs, want):
+        assert np.array_equal(votes.cpu().numpy(), w)
 
 
 def test_one_list_too_long_is_refused():
