@@ -283,7 +283,7 @@ struct JobDesc {
     int32_t layout;            // FP_LAYOUT_PACKED, FP_LAYOUT_COMPACT or FP_LAYOUT_BLOCKED
     int32_t fbits, cbits;      // COMPACT / BLOCKED field widths
     int32_t refill_min;        // idle lanes of a wavefront that trigger a refill
-    int32_t block_bytes;       // block layouts: bytes of a block as the kernel reads it
+    int32_t block_bytes;       // bytes the kernel fetches at a time: a block, or PACKED nodes (one, or two: pairs)
     int32_t F;                 // feature columns of a row (the forest's n_features)
     int32_t stage_rows;        // 1: stage tiles with whole-row 16-byte loads through imap
     int32_t off_imap;          // LDS: column -> compacted feature (int16, -1 unused), 4 * ceil(F / 4) entries

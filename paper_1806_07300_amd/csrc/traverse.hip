@@ -57,6 +57,10 @@ constexpr int32_t kDone = INT32_MIN;
 // 1,024 trees: at 16 lanes 342 us, at 48 308; 10^6 rows x 32 trees 245 and
 // 230); node steps are short (2,000 rows x 64 trees: 52 and 59 us).
 constexpr int kDefaultRefillLanes = 16, kDefaultRefillLanesBlocks = 48;
+// Levels below a bin's top region from which on PACKED nodes are fetched in
+// pairs (run_tile), and the same for launches too small to hide one walk's
+// latency behind another's (few walks, or few threads a workgroup).
+constexpr double kPairDepth = 7.0, kPairDepthIdle = 8.5;
 constexpr int kStageBatch = 4;  // row loads a thread issues before scattering them (tile staging)
 
 // ---------------------------------------------------------------------------
@@ -429,13 +433,14 @@ struct TileRows {
     }
 };
 
-// What a kernel walks: a node layout, blocks in their host form, or blocks in
+// What a kernel walks: a node layout (PACKED nodes one by one or in pairs),
+// blocks in their host form, or blocks in
 // a walk form (with an fp16 tile: X); one kernel each, so that a launch
 // fetches only its own code and the compiler knows the block's shape.
 // kKindAnyNode, kKindAnyBlock: decided per job (batched launches).
 enum Kind : int {
     kKindPacked, kKindCompact, kKindHost48, kKindHost64, kKind64, kKind48h, kKind48hX, kKind48b, kKind48f, kKind32h,
-    kKind32hX, kKindAnyNode, kKindAnyBlock
+    kKind32hX, kKindPairs, kKindAnyNode, kKindAnyBlock
 };
 constexpr int32_t kind_form(int kind) {
     return kind == kKind64                           ? (int32_t)fp::kWalk64
@@ -447,7 +452,7 @@ constexpr int32_t kind_form(int kind) {
 }
 __host__ __device__ __forceinline__ int job_kind(const JobDesc& j) {
     return j.layout == FP_LAYOUT_COMPACT       ? kKindCompact
-           : j.layout < FP_LAYOUT_BLOCKED      ? kKindPacked
+           : j.layout < FP_LAYOUT_BLOCKED      ? (j.block_bytes == 2 * (int)sizeof(Node16) ? kKindPairs : kKindPacked)
            : j.form == fp::kWalk64             ? kKind64
            : j.form == fp::kWalk48h            ? (j.x16 ? kKind48hX : kKind48h)
            : j.form == fp::kWalk48b            ? kKind48b
@@ -504,7 +509,7 @@ __device__ __forceinline__ int stage_group(const JobDesc& j, int group, unsigned
     const int t_lo = b_lo * j.bin_size;
     const int nt = (int)min((int64_t)b_hi * j.bin_size, (int64_t)j.n_trees) - t_lo;
     constexpr bool any = KIND == kKindAnyNode || KIND == kKindAnyBlock;
-    constexpr bool blk = KIND != kKindPacked && KIND != kKindCompact && KIND != kKindAnyNode;
+    constexpr bool blk = KIND != kKindPacked && KIND != kKindPairs && KIND != kKindCompact && KIND != kKindAnyNode;
     const int32_t form = KIND == kKindAnyBlock ? j.form : kind_form(KIND);
     // PACKED: the bin's top nodes; block layouts: its first blocks (roots
     // first), as 16-byte pieces; cap pieces per bin
@@ -576,15 +581,18 @@ __device__ __forceinline__ int stage_group(const JobDesc& j, int group, unsigned
 }
 
 // FMODE: 0 features from memory, 1 features in LDS, 2 decided by j.feat_lds.
-// A deep node is fetched with the one that follows it in Stat order, the
-// likely next of its walk: a line fetched from beyond L1 costs 2.4 cycles of
-// the CU (L2) to 11 (beyond), a further 16 bytes of it 0.7 (100,003 rows x 64
-// trees at their best tiles: single nodes 238 us, two 214, three 239, four
-// 253; 2,000 rows: 18.0, 15.2, 14.6, 15.0).  Four cursors or more per lane
-// have no registers for that and fetch single nodes.
-template <int K, int FMODE>
+// PAIRS: a deep node is fetched with the one that follows it in Stat order,
+// the likely next of its walk: a line fetched from beyond L1 costs 2.4 cycles
+// of the CU (L2) to 11 (beyond), a further 16 bytes of it 0.7 (100,003 rows x
+// 64 trees at their best tiles: single nodes 238 us, two 214, three 239, four
+// 253; 2,000 rows: 18.0, 15.2, 14.6, 15.0).  Only where walks go on deep below
+// staged top nodes and features are in LDS (resolve_job): 100,000 rows x 600
+// trees of depth 6, 64-row tiles: single 523 us, pairs 814; features in
+// memory, 128 trees of depth 10: 650 and 821.  Four cursors or more per lane
+// have no registers for it.
+template <int K, int FMODE, bool PAIRS>
 __device__ __forceinline__ void run_tile(const JobDesc& j, int nt, int tile, unsigned char* smem) {
-    constexpr int kRun = K <= 2 ? 2 : 1;
+    constexpr int kRun = PAIRS ? 2 : 1;
     const bool feat_lds = FMODE == 2 ? (j.feat_lds != 0) : (FMODE == 1);
     const Node16* top = reinterpret_cast<const Node16*>(smem);
     const int4* ttab = reinterpret_cast<const int4*>(smem + j.off_ttab);
@@ -1489,7 +1497,7 @@ __device__ __forceinline__ void stage_kind(const JobDesc& j, int tile, unsigned 
 // layouts: one), and writes its votes.
 template <int K, int FMODE, int KIND>
 __device__ __forceinline__ void walk_tile(const JobDesc& j, int nt, int tile, unsigned char* smem) {
-    if constexpr (KIND == kKindPacked) run_tile<K, FMODE>(j, nt, tile, smem);
+    if constexpr (KIND == kKindPacked || KIND == kKindPairs) run_tile<K, FMODE, KIND == kKindPairs>(j, nt, tile, smem);
     else if constexpr (KIND == kKindCompact) run_tile_compact<K, FMODE>(j, nt, tile, smem);
     else if constexpr (KIND == kKindHost48 || KIND == kKindHost64) run_tile_blocked<1, FMODE, KIND == kKindHost48>(j, nt, tile, smem);
     else run_tile_walk<FMODE, kind_form(KIND), KIND == kKind48hX || KIND == kKind32hX>(j, nt, tile, smem);
@@ -1504,6 +1512,7 @@ __device__ __forceinline__ void walk_tile(const JobDesc& j, int nt, int tile, un
 template <int K, int KIND>
 struct MinWaves {
     static constexpr int value = KIND == kKindPacked ? (K <= 4 ? 8 : 4) : KIND == kKindCompact ? (K <= 2 ? 8 : 4) : 8;
+    static_assert(KIND != kKindPairs || K <= 2, "four cursors or more have no registers for pairs");
 };
 
 template <int K, int FMODE, int KIND>
@@ -1543,8 +1552,17 @@ __device__ __forceinline__ void item_tiles(const JobDesc& j, const WorkItem& w, 
     const int kind = job_kind(j);
     for (int tile = w.tile_begin; tile < w.tile_end; tile++) {
         if constexpr (!BLOCKS) {
-            if (kind == kKindCompact) item_tile<K, FM, kKindCompact>(j, nt, tile, smem);
-            else item_tile<K, FM, kKindPacked>(j, nt, tile, smem);
+            if (kind == kKindCompact) {
+                item_tile<K, FM, kKindCompact>(j, nt, tile, smem);
+                continue;
+            }
+            if constexpr (FM == 1 && K <= 2) {
+                if (kind == kKindPairs) {
+                    item_tile<K, 1, kKindPairs>(j, nt, tile, smem);
+                    continue;
+                }
+            }
+            item_tile<K, FM, kKindPacked>(j, nt, tile, smem);
         } else {
             switch (kind) {
                 case kKindHost48: item_tile<1, FM, kKindHost48>(j, nt, tile, smem); break;
@@ -1667,6 +1685,9 @@ const void* pick_packed(int K, int fmode, int kind) {
         case kKind32h: return packed_fn<1, kKind32h>(fmode);
         case kKind48hX: return reinterpret_cast<const void*>(&packed_kernel<1, 1, kKind48hX>);
         case kKind32hX: return reinterpret_cast<const void*>(&packed_kernel<1, 1, kKind32hX>);
+        case kKindPairs:
+            if (K == 1) return reinterpret_cast<const void*>(&packed_kernel<1, 1, kKindPairs>);
+            if (K == 2) return reinterpret_cast<const void*>(&packed_kernel<2, 1, kKindPairs>);
     }
 #define FP_PICK(KK) \
     if (K == KK) return kind == kKindCompact ? packed_fn<KK, kKindCompact>(fmode) : packed_fn<KK, kKindPacked>(fmode);
@@ -1898,6 +1919,14 @@ int resolve_job(const fp_packed* p, const fp_tune* t, const float* X, int64_t n_
         j->cap = (int32_t)(std::min<size_t>(top_nodes / bpg / bw, (size_t)max_blocks) * bw);
     } else {
         j->cap = (int32_t)std::min<size_t>(top_nodes / bpg, (size_t)h.max_top_len);
+        // PACKED nodes come in pairs where walks are long below the top region
+        // and nothing but those deep nodes is read from memory (top nodes of a
+        // bin's trees are interleaved: the next one is another tree's)
+        const double deep = h.expected_depth - (h.interleave_depth + 1);
+        const bool busy = n_rows * h.n_trees >= (1 << 18) && (t->block_threads == 0 || t->block_threads >= 512);
+        const bool pairs = h.layout == FP_LAYOUT_PACKED && j->feat_lds && j->cap >= h.max_top_len &&
+                           deep >= (busy ? kPairDepth : kPairDepthIdle);
+        j->block_bytes = pairs ? 2 * (int32_t)sizeof(Node16) : (int32_t)sizeof(Node16);
     }
     job_lds_layout(j);
     return FP_OK;
