@@ -261,22 +261,27 @@ int fp_infer_cardinality(const fp_forest_view *forest, const float *X_dev, int64
  * Launch parameters of the traversal kernels (the GPU form of assigning bins
  * to workers, Sec. III, and of Bin+ round-robin evaluation, Sec. III-B).
  *   rows_per_block  most observations per workgroup (packed layouts; 1..4096;
- *                   0: in fp_predict as many as give each CU a tile, up to
- *                   512 (node layouts: 256), in plans 16 to 64 (node layouts
- *                   and the server: 16), fewer until the workgroup's LDS
- *                   tables fit, e.g. for thousands of classes).  fp_predict
- *                   spreads the rows of a block layout evenly over the rounds
- *                   of tiles that this size needs
+ *                   0: in fp_predict as many as give each CU a tile (node
+ *                   layouts two), up to 512 (PACKED 256, COMPACT 64; with
+ *                   features read from memory 16), in plans 16 to 64 (node
+ *                   layouts and the server: 16), fewer until the workgroup's
+ *                   LDS tables fit, e.g. for thousands of classes).  fp_predict
+ *                   spreads the rows of a block layout, and those of an
+ *                   automatic tile, evenly over the rounds of tiles that this
+ *                   size needs
  *   cursors         trees a lane walks concurrently, round-robin (1, 2, 4, 8;
  *                   0: 1 in fp_predict, a plan's own elsewhere);
  *                   BLOCKED walks one block per lane and ignores it
  *   tree_groups     bins are split into this many groups, each group handled
  *                   by its own workgroups (votes then merge with atomics);
- *                   0: one group, or in fp_predict, for at least 2^18 walks,
- *                   up to 8 in a block layout of at least 512 trees or a node
- *                   layout of more than 4 MB
- *   block_threads   workgroup size (64..1024, multiple of 64; 0: 1024 in block
- *                   layouts, 512 in node layouts, 256 in the naive layout)
+ *                   groups that would hold no bin are left out.  0: one group,
+ *                   or in fp_predict, for at least 2^18 walks, up to 8 in a
+ *                   forest of more than 4 MB (COMPACT 8 MB; block layouts from
+ *                   512 trees on) whose walks outweigh staging every row once
+ *                   per group, and where explicit tiles leave CUs idle
+ *   block_threads   workgroup size (64..1024, multiple of 64; 0: 1024; node
+ *                   layouts 512 for explicit tiles and for tiles of few walks;
+ *                   256 in the naive layout)
  *   lds_top_nodes   bin-top nodes staged in LDS (0: the whole top region as far
  *                   as LDS allows; -1: none)
  *   feature_lds     1: stage the observation tile in LDS (FP_E2BIG if it cannot

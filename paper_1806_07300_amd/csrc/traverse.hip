@@ -57,6 +57,10 @@ constexpr int32_t kDone = INT32_MIN;
 // 1,024 trees: at 16 lanes 342 us, at 48 308; 10^6 rows x 32 trees 245 and
 // 230); node steps are short (2,000 rows x 64 trees: 52 and 59 us).
 constexpr int kDefaultRefillLanes = 16, kDefaultRefillLanesBlocks = 48;
+// Rows of an automatic tile whose features stay in memory: the rows of a tile
+// are read from L1, which holds few (30,000 image rows x 128 trees: 16-row
+// tiles 340 us, 118-row ones 1420).
+constexpr int kMemoryTileRows = 16;
 // Levels below a bin's top region from which on PACKED nodes are fetched in
 // pairs (run_tile), and the same for launches too small to hide one walk's
 // latency behind another's (few walks, or few threads a workgroup).
@@ -1511,7 +1515,9 @@ __device__ __forceinline__ void walk_tile(const JobDesc& j, int nt, int tile, un
 // than 128 VGPRs.
 template <int K, int KIND>
 struct MinWaves {
-    static constexpr int value = KIND == kKindPacked ? (K <= 4 ? 8 : 4) : KIND == kKindCompact ? (K <= 2 ? 8 : 4) : 8;
+    static constexpr int value = KIND == kKindPacked    ? (K <= 4 ? 8 : 4)
+                                 : KIND == kKindCompact ? (K <= 2 ? 8 : K == 4 ? 6 : 4)
+                                                        : 8;
     static_assert(KIND != kKindPairs || K <= 2, "four cursors or more have no registers for pairs");
 };
 
@@ -1780,21 +1786,45 @@ int resolve_job(const fp_packed* p, const fp_tune* t, const float* X, int64_t n_
     if (t->rows_per_block > 4096) return fp_set_error(FP_EINVAL, "rows_per_block %d exceeds 4096", t->rows_per_block);
     // tree_groups 0: one, except for launches of their own (cus > 0) of at
     // least 2^18 walks, which pay for zeroing the votes and the classes' own
-    // launch:
+    // launch, on forests larger than an XCD's L2 (4 MB; 600 trees of 0.4 MB,
+    // 4,000 rows: one group 20.5 us, four 26.3; COMPACT 8 MB: 100,000 rows x
+    // 256 trees of 4.3 MB: one group 510 us, eight 548):
     //  - block layouts of 512 trees or more: a group per 128 trees, so that a
     //    workgroup's LDS holds several blocks of each of its trees instead of
     //    one or none (4,096 rows x 1,024 trees: one group 60 us at its best
     //    tile, eight 47; 40,000 rows: 382 and 337);
-    //  - node layouts larger than an XCD's L2 (4 MB): up to 8 groups, which
-    //    workgroup numbers spread over the XCDs, so that each L2 sees only its
-    //    groups' nodes (100,003 rows x 64 trees, 20 MB: one group 285 us at
-    //    its best tile, four 214), unless staging every row once per group
-    //    costs more (10,000 image rows x 128 trees: one 62 us, eight 76)
+    //  - node layouts: 8, 4 or 2 groups, which workgroup numbers spread over
+    //    the 8 XCDs, so that each L2 sees only its groups' nodes (100,003 rows
+    //    x 64 trees, 20 MB: one group 285 us at its best tile, four 214); as
+    //    many as hold a like number of bins each (9 bins: two groups 690 us,
+    //    five 767).
+    // Every row is staged, and its votes added, once per group: not where
+    // that outweighs the walks (30,000 rows x 2,000 columns x 640 trees: one
+    // group 403 us, five 600; 10,000 image rows x 128 trees: 62 and, with
+    // eight, 76); nor where a group's explicit tile has fewer walks than the
+    // workgroup threads (100,000 rows x 64 trees, 16-row tiles: one 311 us,
+    // four 398).  Explicit tiles that leave CUs idle take groups for those
+    // (4,000 rows x 600 trees, 64-row tiles: one 55 us, four 24), and, within
+    // a tighter bound on staging, for wavefronts that smaller workgroups leave
+    // idle (128 trees, 16-row tiles in 256 threads, 64 columns: 40 classes,
+    // one 50 us, two 33; 100 classes 27 and 38).
     int G = std::max(1, t->tree_groups);
+    const int threads = t->block_threads > 0 ? t->block_threads : 1024;
     if (t->tree_groups <= 0 && cus > 0 && t->tree_passes <= 1 && n_rows * h.n_trees >= (1 << 18)) {
-        const int bins8 = std::min(8, h.n_bins);
-        if (blocks) G = std::max(1, h.n_trees >= 512 ? std::min(8, h.n_trees / 128) : 1);
-        else if (h.total_bytes > (int64_t(4) << 20) && (int64_t)h.n_features * bins8 <= 4 * (int64_t)h.n_trees) G = bins8;
+        auto staged = [&](int64_t g, int64_t most) { return (h.n_features + h.n_classes) * g <= most * h.n_trees; };
+        if (h.total_bytes > (int64_t(h.layout == FP_LAYOUT_COMPACT ? 8 : 4) << 20)) {
+            auto bins_of = [&](int g) { return (h.n_bins + g - 1) / g; };
+            if (blocks) G = std::max(1, h.n_trees >= 512 ? std::min(8, h.n_trees / 128) : 1);
+            else for (G = 8; G > 1 && (bins_of(bins_of(G)) != G || 5 * h.n_bins < 4 * G * bins_of(G));) G /= 2;
+            if (!staged(G, 3)) G = 1;
+            while (!auto_R && G > 1 && (int64_t)t->rows_per_block * h.n_trees < (int64_t)threads * G) G /= 2;
+        }
+        if (!auto_R) {
+            const int64_t tiles = (n_rows + t->rows_per_block - 1) / t->rows_per_block;
+            int64_t idle = std::min<int64_t>(8, (int64_t)cus * (1024 / threads) / tiles);
+            while (idle > 1 && !staged(idle, 2)) idle /= 2;
+            G = (int)std::max({(int64_t)G, std::min<int64_t>(8, cus / tiles), idle});
+        }
     }
     if (G > h.n_bins) G = h.n_bins;
     int P = t->tree_passes > 0 ? t->tree_passes : 1;
@@ -1802,24 +1832,41 @@ int resolve_job(const fp_packed* p, const fp_tune* t, const float* X, int64_t n_
     const int bpg = (h.n_bins + P * G - 1) / (P * G);
     // passes that would hold no bin are dropped: the last pass writes the classes
     P = ((h.n_bins + bpg - 1) / bpg + G - 1) / G;
+    if (P == 1) G = (h.n_bins + bpg - 1) / bpg;  // nor do groups without a bin take workgroups
     const int tpg = (int)std::min<int64_t>((int64_t)bpg * h.bin_size, h.n_trees);
-    // rows_per_block 0, alone on the device: a tile per CU.  Fewer, larger
-    // tiles leave CUs idle (300 image rows x 128 trees: 16-row tiles 15.9 us,
-    // 2-row ones 10.8); smaller ones stage the trees' tops and wait for their
-    // last walks more often (4,096 rows x 1,024 trees: 8-row tiles 71 us,
-    // 16-row ones 60; 10^6 rows x 32 trees: 16-row tiles 558 us, 128-row ones
-    // 270, 512-row ones 241).  At most 16,384 walks and 512 rows for blocks,
-    // 256 rows for nodes; with tree groups two (nodes: five) workgroups a CU.
+    // rows_per_block 0, alone on the device.  Fewer, larger tiles leave CUs
+    // idle (300 image rows x 128 trees: 16-row tiles 15.9 us, 2-row ones
+    // 10.8); smaller ones stage the trees' tops and wait for their last walks
+    // more often (4,096 rows x 1,024 trees: 8-row tiles 71 us, 16-row ones 60;
+    // 10^6 rows x 32 trees: 16-row tiles 558 us, 128-row ones 270, 512-row
+    // ones 241).
+    //  - blocks: a tile per CU (with tree groups two), at most 16,384 walks
+    //    and 512 rows;
+    //  - nodes: two tiles per CU (4,000 rows x 272 trees, COMPACT: one 43 us,
+    //    two 35), or one where two would not have a walk for each of their
+    //    threads; at most 256 rows, COMPACT 64 (its top nodes come from
+    //    memory: 100,000 rows x 600 trees: 256-row tiles 618 us, 64-row ones
+    //    525);
+    //  - features in memory: at most kMemoryTileRows.
+    // With 512 threads or fewer twice the tiles (not with four cursors or
+    // more, which hold half the wavefronts; COMPACT, 256 threads: 16 rows).
     // A plan's jobs share the device: 16 to 64 rows, 64 tiles or more (16
     // forests of up to 512 trees and 60,000 rows: 16-row tiles 488 us, 32-row
     // ones 393, 64-row ones 333; 8 forests, 10,000 rows: 78, 58 and 58).
     // Node layouts there, and serving, take 16.
-    const int64_t most = blocks ? std::min<int64_t>(512, std::max<int64_t>(32, 16384 / tpg)) : 256;
-    const int64_t per_cu = G == 1 ? 1 : blocks ? 2 : 5;
-    int R = !auto_R    ? t->rows_per_block
-            : cus > 0  ? (int)std::min(most, std::max<int64_t>(G > 1 ? 16 : 1, (n_rows * G + per_cu * cus - 1) / (per_cu * cus)))
-            : cus == 0 && blocks ? (int)std::min<int64_t>(64, std::max<int64_t>(16, n_rows / 64))
-                       : 16;
+    const int64_t most = t->feature_lds < 0                ? kMemoryTileRows
+                         : cus <= 0                        ? 64
+                         : blocks                          ? std::min<int64_t>(512, std::max<int64_t>(32, 16384 / tpg))
+                         : h.layout == FP_LAYOUT_COMPACT   ? (threads <= 256 ? 16 : 64)
+                                                           : 256;
+    const int64_t slots = (int64_t)cus * (threads <= 512 && t->cursors < 4 ? 2 : 1);
+    auto rows_for = [&](int64_t per_cu) { return (n_rows * G + per_cu * slots - 1) / (per_cu * slots); };
+    int64_t want = 16;
+    if (cus > 0 && G > 1) want = std::max<int64_t>(16, rows_for(2));
+    else if (cus > 0 && blocks) want = rows_for(1);
+    else if (cus > 0) want = std::max(rows_for(2), std::min<int64_t>((n_rows + cus - 1) / cus, (threads + tpg - 1) / tpg));
+    else if (cus == 0 && blocks) want = std::min<int64_t>(64, std::max<int64_t>(16, n_rows / 64));
+    int R = auto_R ? (int)std::min(most, want) : t->rows_per_block;
     if ((int64_t)R * tpg >= (1 << 30)) return fp_set_error(FP_E2BIG, "rows_per_block x trees per group too large");
     const uint8_t* base = static_cast<const uint8_t*>(p->dev);
     memset(j, 0, sizeof *j);
@@ -1875,36 +1922,48 @@ int resolve_job(const fp_packed* p, const fp_tune* t, const float* X, int64_t n_
         j->stage_rows = feat && ld % 4 == 0 && reinterpret_cast<uintptr_t>(X) % 16 == 0 && h.n_features <= 4096;
         return job_lds_layout(j);
     };
-    // An automatic tile of a node layout shares a CU with three others of 512
-    // threads: half of the LDS that a block layout's 1024 threads take
-    if (auto_R && !blocks && cus > 0 && size_for(1, t->feature_lds >= 0) <= lds_block / 2) lds_block /= 2;
+    // An automatic tile of a node layout in workgroups of 512 threads or fewer
+    // shares a CU with three others: half of the LDS that 1,024 threads take
+    if (auto_R && !blocks && cus > 0 && threads <= 512 && t->cursors < 4 && t->lds_bytes == 0 &&
+        t->feature_lds >= 0 && size_for(1, true) <= lds_block / 2)
+        lds_block /= 2;
     // fit by shrinking an automatic tile first (features in LDS matter most),
     // then by reading features from memory.  An automatic tile leaves LDS for
     // a block per tree, up to an eighth of the budget, or for half of the
-    // bins' top nodes
+    // bins' top nodes (these only beyond 8 rows: 30,000 rows x 2,000 columns x
+    // 640 trees, PACKED: 4 rows and tops 681 us, 8 rows 585)
     const size_t tops = !auto_R                         ? 0
                         : blocks                        ? std::min(lds_block / 8, (size_t)tpg * (size_t)j->block_bytes)
                         : h.layout == FP_LAYOUT_COMPACT ? 0
                         : cus > 0 ? std::min(lds_block / 2, (size_t)bpg * (size_t)h.max_top_len * sizeof(Node16)) : 0;
     auto fit = [&](bool feat) {
-        size_t need = size_for(R, feat);
+        const size_t need = size_for(R, feat);
         if (!auto_R || need + (feat ? tops : 0) <= lds_block) return need;
-        int lo = 1, hi = R;  // the largest tile that fits (1 if none does)
-        while (hi - lo > 1) {
-            const int r = (lo + hi) / 2;
-            if (size_for(r, feat) + (feat ? tops : 0) <= lds_block) lo = r;
-            else hi = r;
-        }
-        return size_for(lo, feat);
+        auto largest = [&](int most_r, size_t leave) {  // the largest tile that fits (1 if none does)
+            int lo = 1, hi = most_r + 1;
+            while (hi - lo > 1) {
+                const int r = (lo + hi) / 2;
+                if (size_for(r, feat) + leave <= lds_block) lo = r;
+                else hi = r;
+            }
+            return lo;
+        };
+        const int r = largest(R, feat ? tops : 0);
+        return size_for(blocks || r >= 8 ? r : largest(std::min(R, 8), 0), feat);
     };
     size_t need = fit(t->feature_lds >= 0);
     if (need > lds_block) {
         if (t->feature_lds >= 1)
             return fp_set_error(FP_E2BIG, "observation tile of %d rows x %d columns does not fit in %zu bytes of LDS",
                                 R, j->Fc, lds_block);
+        if (auto_R) R = (int)std::min<int64_t>(R, kMemoryTileRows);
         need = fit(false);
         if (need > lds_block)
             return fp_set_error(FP_E2BIG, "per-workgroup tables of %zu bytes exceed %zu bytes of LDS", need, lds_block);
+    } else if (auto_R && !blocks && cus > 0 && tpg <= 1024 && j->R * tpg > 1024 && j->R * tpg < 8 * 1024 / 7) {
+        // a walk per thread rather than a second round of few (30,000 rows x
+        // 2,000 columns x 128 trees: 9-row tiles 143 us, 8-row ones 120)
+        need = size_for(1024 / tpg, j->feat_lds != 0);
     }
     // LDS left over holds the hottest nodes: PACKED bin tops, or the first
     // blocks of each BLOCKED bin (its trees' root blocks come first), counted
@@ -1923,7 +1982,7 @@ int resolve_job(const fp_packed* p, const fp_tune* t, const float* X, int64_t n_
         // and nothing but those deep nodes is read from memory (top nodes of a
         // bin's trees are interleaved: the next one is another tree's)
         const double deep = h.expected_depth - (h.interleave_depth + 1);
-        const bool busy = n_rows * h.n_trees >= (1 << 18) && (t->block_threads == 0 || t->block_threads >= 512);
+        const bool busy = n_rows * h.n_trees >= (1 << 18) && threads >= 512;
         const bool pairs = h.layout == FP_LAYOUT_PACKED && j->feat_lds && j->cap >= h.max_top_len &&
                            deep >= (busy ? kPairDepth : kPairDepthIdle);
         j->block_bytes = pairs ? 2 * (int32_t)sizeof(Node16) : (int32_t)sizeof(Node16);
@@ -2110,14 +2169,20 @@ static int predict_impl(const fp_packed* p, const fp_tune* tune, const float* X,
     rc = fp::device_props(dev, &dp);
     if (rc) return rc;
     hipStream_t stream = static_cast<hipStream_t>(stream_v);
-    // block layouts: 16 waves a workgroup, which share its tile and first
-    // blocks (20,001 rows x 784 features x 256 trees, 16-row tiles: 256
-    // threads 142 us, 1024 threads 102); node layouts 8 (2,000 rows x 64
-    // trees, 8-row tiles: 256 threads 21 us, 512 threads 15)
-    const int threads = tune && tune->block_threads > 0   ? tune->block_threads
-                        : h.layout >= FP_LAYOUT_BLOCKED   ? 1024
-                        : h.layout == FP_LAYOUT_NAIVE     ? 256
-                                                          : 512;
+    // 16 waves a workgroup share its tile and the trees' tops (20,001 rows x
+    // 784 features x 256 trees in blocks, 16-row tiles: 256 threads 142 us,
+    // 1024 threads 102; COMPACT, 30,000 rows x 353 columns x 128 trees: 512
+    // threads 168 us, 1024 threads 145).  In node layouts 8 for explicit tiles
+    // and, with four cursors or more, which hold half the wavefronts, 8 (4
+    // for many rows of a COMPACT forest that do not fill LDS); 8 for many rows
+    // whose features come from memory: the L1 holds few of their lines
+    const bool nodes = h.layout < FP_LAYOUT_BLOCKED, many = n_rows >= 16 * (int64_t)dp.cus;
+    int threads = tune && tune->block_threads > 0                              ? tune->block_threads
+                  : h.layout == FP_LAYOUT_NAIVE                                ? 256
+                  : tune && nodes && tune->cursors >= 4
+                      ? (h.layout == FP_LAYOUT_COMPACT && many && h.n_used_features <= 512 ? 256 : 512)
+                  : tune && ((nodes && tune->rows_per_block > 0) || (many && tune->feature_lds < 0)) ? 512
+                                                                               : 1024;
     if (threads % 64 || threads < 64 || threads > 1024)
         return fp_set_error(FP_EINVAL, "block_threads %d must be a multiple of 64 in [64, 1024]", threads);
 
@@ -2145,14 +2210,25 @@ static int predict_impl(const fp_packed* p, const fp_tune* tune, const float* X,
     const size_t lds_block = tune && tune->lds_bytes > 0      ? std::min((size_t)tune->lds_bytes, lds_max)
                              : tune && tune->lds_top_nodes > 0 ? lds_max
                                                                : fp::default_lds_block(dp);
+    fp_tune at = tune ? *tune : fp_tune{};
+    at.block_threads = threads;
     fp::JobDesc j;
-    rc = fp::resolve_job(p, tune, X, n_rows, ld, votes, cls, lds_block, dp.cus, &j);
+    rc = fp::resolve_job(p, &at, X, n_rows, ld, votes, cls, lds_block, dp.cus, &j);
     if (rc) return rc;
+    // 8 wavefronts also for an automatic tile that has far fewer walks than
+    // 1,024 (nodes), or of few rows in half of the usual LDS, which leaves
+    // room for two more workgroups a CU
+    if (!(tune && tune->block_threads > 0) && threads == 1024 && at.rows_per_block <= 0 &&
+        (nodes ? j.R * j.trees_per_group < 768 : j.R < 16 && 2 * lds_block <= fp::default_lds_block(dp))) {
+        threads = at.block_threads = 512;
+        rc = fp::resolve_job(p, &at, X, n_rows, ld, votes, cls, lds_block, dp.cus, &j);
+        if (rc) return rc;
+    }
     int occ = 1;
     rc = fp::packed_occupancy(K, j, threads, &occ);
     if (rc) return rc;
     const int64_t resident = std::max<int64_t>(1, (int64_t)dp.cus * occ / j.G);  // workgroups of a group
-    if (h.layout >= FP_LAYOUT_BLOCKED && j.n_tiles > resident) {
+    if ((!nodes || at.rows_per_block <= 0) && j.n_tiles > resident) {
         // full rounds of tiles: rows spread evenly, so that the last round
         // does not leave most workgroups idle (2M rows in 768-row tiles, 10.2
         // rounds of 256: 7.04 ms, 11 full ones 6.38).  An automatic tile may
@@ -2161,7 +2237,7 @@ static int predict_impl(const fp_packed* p, const fp_tune* tune, const float* X,
         const bool grow = !tune || tune->rows_per_block <= 0;
         const int64_t rounds = (j.n_tiles + resident - 1) / resident;
         for (int64_t r = grow && rounds <= 4 ? rounds - 1 : rounds; r <= rounds; r++) {
-            fp_tune even = tune ? *tune : fp_tune{};
+            fp_tune even = at;
             even.rows_per_block = (int32_t)std::min<int64_t>(4096, (n_rows + r * resident - 1) / (r * resident));
             if (even.rows_per_block == j.R || even.rows_per_block > j.R + j.R / 4) continue;
             fp::JobDesc e;
