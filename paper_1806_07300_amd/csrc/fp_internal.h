@@ -331,7 +331,8 @@ size_t job_lds_layout(JobDesc* j);
 // Fill `j` for forest p, launch parameters t (threads and cursors decided by
 // the caller), rows X.  `lds_block` caps the job's LDS footprint (bytes); `cus`
 // > 0: the job has a launch, and that many CUs, to itself; 0: it shares one;
-// -1: it shares one and its latency counts (serving).
+// -1: it shares one and its latency counts (serving).  t->block_threads is the
+// launch's workgroup size.
 int resolve_job(const fp_packed* p, const fp_tune* t, const float* X, int64_t n_rows, int64_t ld,
                 int32_t* votes, int32_t* cls, size_t lds_block, int cus, JobDesc* j);
 

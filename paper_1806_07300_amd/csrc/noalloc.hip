@@ -92,6 +92,7 @@ extern "C" int fp_predict_batched_noalloc(const fp_job* jobs, int32_t n_jobs, co
         fp_tune t = jb.forest->tune;
         fp_tune rec;
         if (jb.n_rows > 0 && fp::launch_tune_get(jb.forest, jb.n_rows, threads, K, &rec)) t = rec;
+        t.block_threads = threads;
         rc = fp::resolve_job(jb.forest, &t, jb.X, jb.n_rows, jb.ld, jb.votes, jb.cls, lds_block, 0, &jd[i]);
         if (rc) return rc;
         fp::flatten_passes(&jd[i]);

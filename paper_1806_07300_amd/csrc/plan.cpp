@@ -179,10 +179,12 @@ extern "C" int fp_plan_create(const fp_job* jobs, int32_t n_jobs, const fp_plan_
                 }
                 // candidates are timed with the default LDS budget: a smaller
                 // plan budget falls back to the forest's own parameters
+                t.block_threads = p->threads;
                 if (fp::resolve_job(jb.forest, &t, jb.X, jb.n_rows, jb.ld, jb.votes, jb.cls, lds_block, 0, &p->jobs[i]) ==
                     FP_E2BIG)
                     t = jb.forest->tune;
             }
+            t.block_threads = p->threads;
             rc = fp::resolve_job(jb.forest, &t, jb.X, jb.n_rows, jb.ld, jb.votes, jb.cls, lds_block, 0, &p->jobs[i]);
             if (rc) {
                 std::string msg = fp_last_error();

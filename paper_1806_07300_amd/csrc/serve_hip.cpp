@@ -111,6 +111,7 @@ class HipExecutor final : public fp::ServeExecutor {
         if (p->dev_id != dev_) return fp_set_error(FP_ENODEV, "forest on device %d, server on device %d", p->dev_id, dev_);
         fp::JobDesc j;  // the forest's launch parameters must fit the server's LDS budget
         fp_tune t = p->tune;
+        t.block_threads = opts_.block_threads;
         return fp::resolve_job(p, &t, nullptr, 1, p->hdr.n_features, nullptr, nullptr, lds_block_, -1, &j);
     }
 
@@ -123,6 +124,7 @@ class HipExecutor final : public fp::ServeExecutor {
         for (size_t i = 0; i < batch.size(); i++) {
             const fp::ServeItem& r = batch[i];
             fp_tune t = r.packed->tune;
+            t.block_threads = opts_.block_threads;
             int rc = fp::resolve_job(r.packed, &t, reinterpret_cast<const float*>(d_x_ + r.x_start), r.n_rows, r.F,
                                      reinterpret_cast<int32_t*>(d_v_ + r.v_start), nullptr, lds_block_, -1, &jobs[i]);
             if (rc) return rc;

@@ -1850,10 +1850,11 @@ int resolve_job(const fp_packed* p, const fp_tune* t, const float* X, int64_t n_
     //  - features in memory: at most kMemoryTileRows.
     // With 512 threads or fewer twice the tiles (not with four cursors or
     // more, which hold half the wavefronts; COMPACT, 256 threads: 16 rows).
-    // A plan's jobs share the device: 16 to 64 rows, 64 tiles or more (16
-    // forests of up to 512 trees and 60,000 rows: 16-row tiles 488 us, 32-row
-    // ones 393, 64-row ones 333; 8 forests, 10,000 rows: 78, 58 and 58).
-    // Node layouts there, and serving, take 16.
+    // A plan's jobs share the device: 16 to 64 rows, 64 tiles of 1,024 threads
+    // or more (16 forests of up to 512 trees and 60,000 rows: 16-row tiles 488
+    // us, 32-row ones 393, 64-row ones 333; 8 forests, 10,000 rows: 78, 58 and
+    // 58; 6 forests, 4,000 rows, 256 threads: 16-row tiles 48 us, 62-row ones
+    // 71).  Node layouts there, and serving, take 16.
     const int64_t most = t->feature_lds < 0                ? kMemoryTileRows
                          : cus <= 0                        ? 64
                          : blocks                          ? std::min<int64_t>(512, std::max<int64_t>(32, 16384 / tpg))
@@ -1865,7 +1866,7 @@ int resolve_job(const fp_packed* p, const fp_tune* t, const float* X, int64_t n_
     if (cus > 0 && G > 1) want = std::max<int64_t>(16, rows_for(2));
     else if (cus > 0 && blocks) want = rows_for(1);
     else if (cus > 0) want = std::max(rows_for(2), std::min<int64_t>((n_rows + cus - 1) / cus, (threads + tpg - 1) / tpg));
-    else if (cus == 0 && blocks) want = std::min<int64_t>(64, std::max<int64_t>(16, n_rows / 64));
+    else if (cus == 0 && blocks) want = std::min<int64_t>(64, std::max<int64_t>(16, n_rows * threads / 65536));
     int R = auto_R ? (int)std::min(most, want) : t->rows_per_block;
     if ((int64_t)R * tpg >= (1 << 30)) return fp_set_error(FP_E2BIG, "rows_per_block x trees per group too large");
     const uint8_t* base = static_cast<const uint8_t*>(p->dev);
