@@ -62,9 +62,14 @@ constexpr int kDefaultRefillLanes = 16, kDefaultRefillLanesBlocks = 48;
 // tiles 340 us, 118-row ones 1420).
 constexpr int kMemoryTileRows = 16;
 // Levels below a bin's top region from which on PACKED nodes are fetched in
-// pairs (run_tile), and the same for launches too small to hide one walk's
-// latency behind another's (few walks, or few threads a workgroup).
-constexpr double kPairDepth = 7.0, kPairDepthIdle = 8.5;
+// pairs (run_tile): in launches of their own (100,000 rows in 64-row tiles: 128
+// trees of depth 10 single 191 us, pairs 188, 768 trees of depth 9 823 and
+// 997), in those too small to hide one walk's latency behind another's (few
+// walks, or few threads a workgroup: 4,000 rows, depth 10, 256 threads: 36 and
+// 43), and in launches that share the device, with their small tiles and two
+// cursors (16 forests of depth 8 to 12 in one plan: from 3 levels on 701 us,
+// from 5 on 761).
+constexpr double kPairDepth = 7.0, kPairDepthIdle = 8.5, kPairDepthShared = 3.0;
 constexpr int kStageBatch = 4;  // row loads a thread issues before scattering them (tile staging)
 
 // ---------------------------------------------------------------------------
@@ -1980,12 +1985,13 @@ int resolve_job(const fp_packed* p, const fp_tune* t, const float* X, int64_t n_
     } else {
         j->cap = (int32_t)std::min<size_t>(top_nodes / bpg, (size_t)h.max_top_len);
         // PACKED nodes come in pairs where walks are long below the top region
-        // and nothing but those deep nodes is read from memory (top nodes of a
-        // bin's trees are interleaved: the next one is another tree's)
+        // and features are in LDS; in a launch of its own only where nothing
+        // but those deep nodes is read from memory (top nodes of a bin's trees
+        // are interleaved: the next one is another tree's)
         const double deep = h.expected_depth - (h.interleave_depth + 1);
         const bool busy = n_rows * h.n_trees >= (1 << 18) && threads >= 512;
-        const bool pairs = h.layout == FP_LAYOUT_PACKED && j->feat_lds && j->cap >= h.max_top_len &&
-                           deep >= (busy ? kPairDepth : kPairDepthIdle);
+        const bool pairs = h.layout == FP_LAYOUT_PACKED && j->feat_lds && (cus <= 0 || j->cap >= h.max_top_len) &&
+                           deep >= (cus <= 0 ? kPairDepthShared : busy ? kPairDepth : kPairDepthIdle);
         j->block_bytes = pairs ? 2 * (int32_t)sizeof(Node16) : (int32_t)sizeof(Node16);
     }
     job_lds_layout(j);
