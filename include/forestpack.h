@@ -467,10 +467,10 @@ int fp_autotune(const fp_forest_view *forest, const float *X_dev, int64_t n_rows
  * persistent kernel whose workgroups pull (forest, tree group, row tiles)
  * work items from a device counter, largest estimated cost first (cost =
  * rows x trees x expected depth, the cost model of Eqs. 1-2).  The launch is
- * captured once in a hipGraph (a kernel for the jobs in block layouts and one
- * for those in node layouts, with vote zeroing before and argmax after them
- * only where tree groups share rows; the counters wrap to zero by themselves)
- * and replayed by fp_predict_batched.
+ * captured once in a hipGraph (one kernel over the jobs in block layouts and
+ * then those in node layouts, with vote zeroing before and argmax after it only
+ * where tree groups share rows; the counters wrap to zero by themselves) and
+ * replayed by fp_predict_batched.
  *
  * fp_job: one forest (uploaded, packed layout) with its rows.  Pointers are
  * fixed when the plan is created and must stay valid while the plan is used:

@@ -352,12 +352,15 @@ constexpr size_t kItemSlotBytes = 16;
 constexpr int kDefaultItemsPerBlock = 16;
 size_t batched_job_budget(size_t lds_block);
 // A batched launch: block-layout jobs (class 0) and node-layout ones (class 1)
-// run in a kernel each, over their own part of the work list.
+// have their own part of the work list.  Launches of one class run in its
+// kernel, launches of both in one that walks first the one part, then the other
+// (`mixed`; lds and resident are then the same for both).
 struct BatchedShape {
     int K = 2, threads = 1024;
     int32_t n_jobs = 0;
     size_t lds[2] = {0, 0};           // the largest job layout
     int64_t resident[2] = {1, 1};     // workgroups that fit the device
+    bool mixed = false;
     bool atomics = false, atomic_classes = false;  // some job's groups add into its votes (and it wants classes)
 };
 inline int batched_class(const JobDesc& j) { return j.layout >= FP_LAYOUT_BLOCKED ? 0 : 1; }

@@ -260,8 +260,10 @@ extern "C" int fp_plan_info_get(const fp_plan* p, fp_plan_info* out) {
     out->n_jobs = (int32_t)p->jobs.size();
     out->n_items = (int32_t)p->items.size();
     const int64_t n_node_items = (int64_t)p->items.size() - p->n_block_items;
-    out->blocks = (int32_t)std::max<int64_t>(1, std::max(std::min<int64_t>(p->shape.resident[0], p->n_block_items),
-                                                         std::min<int64_t>(p->shape.resident[1], n_node_items)));
+    out->blocks = (int32_t)std::max<int64_t>(
+        1, p->shape.mixed ? std::min<int64_t>(p->shape.resident[0], (int64_t)p->items.size())
+                          : std::max(std::min<int64_t>(p->shape.resident[0], p->n_block_items),
+                                     std::min<int64_t>(p->shape.resident[1], n_node_items)));
     out->block_threads = p->threads;
     out->cursors = p->K;
     out->graph = p->exec != nullptr;
