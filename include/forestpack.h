@@ -370,7 +370,8 @@ int fp_predict_tuned(const fp_packed *p, const fp_tune *tune, const float *X_dev
 
 /*
  * The design experiment of Sec. III-A (Fig. 2) for a forest already packed:
- * times candidate launch parameters of p (rows per workgroup, workgroup
+ * times candidate launch parameters of p (first those that fp_predict takes
+ * without a record, written out; then rows per workgroup, workgroup
  * size, cursors, refill threshold, tree groups; with block_threads 0 also a
  * CU's whole LDS for one 1024-thread workgroup and, for a forest larger than
  * the last-level cache, tree passes) on the first min(n_rows, 2^18) rows of

@@ -399,7 +399,12 @@ bool launch_tune_get(const fp_packed* p, int64_t n_rows, int32_t threads, int32_
 void launch_tune_put(const fp_packed* p, int64_t n_rows, int32_t threads, int32_t cursors, const fp_tune& t);
 bool autotune_cache_get(uint64_t key, fp_autotune_result* out);
 void autotune_cache_put(uint64_t key, const fp_autotune_result& r);
-// Times launch candidates of p on the first rows of X; fastest in *best.
+// The launch that fp_predict makes of these rows where only the workgroup size
+// and the cursors are given (0: not), with every parameter written out.
+int default_launch(const fp_packed* p, const float* X, int64_t n_rows, int64_t ld, int32_t threads, int32_t cursors,
+                   int32_t* votes, fp_tune* out);
+// Times launch candidates of p on the first rows of X, the default one among
+// them; fastest in *best.
 int search_launch(const fp_packed* p, const float* X, int64_t n_rows, int64_t ld, int32_t threads, int32_t cursors,
                   hipStream_t stream, fp_tune* best, double* best_ms, int32_t* tried);
 

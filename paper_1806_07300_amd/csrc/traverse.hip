@@ -2201,24 +2201,17 @@ int launch_batched(const BatchedShape& sh, const JobDesc* jobs, const WorkItem* 
 // ---------------------------------------------------------------------------
 // single-forest entry points
 // ---------------------------------------------------------------------------
-static int predict_impl(const fp_packed* p, const fp_tune* tune, const float* X, int64_t n_rows, int64_t ld,
-                        int32_t* votes, int32_t* cls, void* stream_v) {
-    fp_clear_error();
-    if (!p) return fp_set_error(FP_EINVAL, "packed forest is NULL");
+namespace {
+// A launch of one forest in a packed layout: everything that the tune leaves
+// open decided.
+struct Launch {
+    JobDesc j;
+    int K, threads, blocks;
+};
+
+int resolve_launch(const fp_packed* p, const fp_tune* tune, const float* X, int64_t n_rows, int64_t ld, int32_t* votes,
+                   int32_t* cls, const fp::DeviceProps& dp, Launch* L) {
     const fp::Header& h = p->hdr;
-    if (n_rows < 0 || n_rows > INT32_MAX) return fp_set_error(FP_EINVAL, "n_rows %lld outside [0, 2^31)", (long long)n_rows);
-    if (ld < h.n_features) return fp_set_error(FP_EINVAL, "ld %lld < n_features %d", (long long)ld, h.n_features);
-    if (n_rows == 0) return FP_OK;
-    if (!X || !votes) return fp_set_error(FP_EINVAL, "X or votes is NULL");
-    if (!p->dev) return fp_set_error(FP_ENODEV, "packed forest is not uploaded");
-    int dev = -1;
-    int rc = fp::current_device(&dev);
-    if (rc) return rc;
-    if (dev != p->dev_id) return fp_set_error(FP_ENODEV, "forest uploaded to device %d, current device is %d", p->dev_id, dev);
-    fp::DeviceProps dp;
-    rc = fp::device_props(dev, &dp);
-    if (rc) return rc;
-    hipStream_t stream = static_cast<hipStream_t>(stream_v);
     // 16 waves a workgroup share its tile and the trees' tops (20,001 rows x
     // 784 features x 256 trees in blocks, 16-row tiles: 256 threads 142 us,
     // 1024 threads 102; COMPACT, 30,000 rows x 353 columns x 128 trees: 512
@@ -2228,29 +2221,12 @@ static int predict_impl(const fp_packed* p, const fp_tune* tune, const float* X,
     // whose features come from memory: the L1 holds few of their lines
     const bool nodes = h.layout < FP_LAYOUT_BLOCKED, many = n_rows >= 16 * (int64_t)dp.cus;
     int threads = tune && tune->block_threads > 0                              ? tune->block_threads
-                  : h.layout == FP_LAYOUT_NAIVE                                ? 256
                   : tune && nodes && tune->cursors >= 4
                       ? (h.layout == FP_LAYOUT_COMPACT && many && h.n_used_features <= 512 ? 256 : 512)
                   : tune && ((nodes && tune->rows_per_block > 0) || (many && tune->feature_lds < 0)) ? 512
                                                                                : 1024;
     if (threads % 64 || threads < 64 || threads > 1024)
         return fp_set_error(FP_EINVAL, "block_threads %d must be a multiple of 64 in [64, 1024]", threads);
-
-    if (h.layout == FP_LAYOUT_NAIVE) {
-        const uint8_t* base = static_cast<const uint8_t*>(p->dev);
-        NaiveArgs a{reinterpret_cast<const int64_t*>(base + h.table_offset),
-                    reinterpret_cast<const Node16*>(base + h.nodes_offset), X, ld, n_rows, votes, cls, h.n_trees,
-                    h.n_classes};
-        const size_t lds = (size_t)h.n_classes * threads * 4;
-        const bool use_lds = lds <= 32768;
-        const int blocks = (int)((n_rows + threads - 1) / threads);
-        if (use_lds)
-            hipLaunchKernelGGL(naive_kernel<true>, dim3(blocks), dim3(threads), lds, stream, a);
-        else
-            hipLaunchKernelGGL(naive_kernel<false>, dim3(blocks), dim3(threads), 0, stream, a);
-        return check_launch("naive_kernel");
-    }
-
     // one walk per lane: more cost registers and gain nothing (100,003 rows x
     // 64 trees: one 214 us, two 227)
     const int K = tune && tune->cursors > 0 ? tune->cursors : 1;
@@ -2262,8 +2238,8 @@ static int predict_impl(const fp_packed* p, const fp_tune* tune, const float* X,
                                                                : fp::default_lds_block(dp);
     fp_tune at = tune ? *tune : fp_tune{};
     at.block_threads = threads;
-    fp::JobDesc j;
-    rc = fp::resolve_job(p, &at, X, n_rows, ld, votes, cls, lds_block, dp.cus, &j);
+    JobDesc& j = L->j;
+    int rc = fp::resolve_job(p, &at, X, n_rows, ld, votes, cls, lds_block, dp.cus, &j);
     if (rc) return rc;
     // 8 wavefronts also for an automatic tile that has far fewer walks than
     // 1,024 (nodes), or of few rows in half of the usual LDS, which leaves
@@ -2302,7 +2278,53 @@ static int predict_impl(const fp_packed* p, const fp_tune* tune, const float* X,
         }
     }
     const int64_t per_group = std::min<int64_t>(j.n_tiles, resident);
-    const int blocks = (int)std::max<int64_t>(1, per_group) * j.G;
+    L->K = K;
+    L->threads = threads;
+    L->blocks = (int)std::max<int64_t>(1, per_group) * j.G;
+    return FP_OK;
+}
+}  // namespace
+
+static int predict_impl(const fp_packed* p, const fp_tune* tune, const float* X, int64_t n_rows, int64_t ld,
+                        int32_t* votes, int32_t* cls, void* stream_v) {
+    fp_clear_error();
+    if (!p) return fp_set_error(FP_EINVAL, "packed forest is NULL");
+    const fp::Header& h = p->hdr;
+    if (n_rows < 0 || n_rows > INT32_MAX) return fp_set_error(FP_EINVAL, "n_rows %lld outside [0, 2^31)", (long long)n_rows);
+    if (ld < h.n_features) return fp_set_error(FP_EINVAL, "ld %lld < n_features %d", (long long)ld, h.n_features);
+    if (n_rows == 0) return FP_OK;
+    if (!X || !votes) return fp_set_error(FP_EINVAL, "X or votes is NULL");
+    if (!p->dev) return fp_set_error(FP_ENODEV, "packed forest is not uploaded");
+    int dev = -1;
+    int rc = fp::current_device(&dev);
+    if (rc) return rc;
+    if (dev != p->dev_id) return fp_set_error(FP_ENODEV, "forest uploaded to device %d, current device is %d", p->dev_id, dev);
+    fp::DeviceProps dp;
+    rc = fp::device_props(dev, &dp);
+    if (rc) return rc;
+    hipStream_t stream = static_cast<hipStream_t>(stream_v);
+    if (h.layout == FP_LAYOUT_NAIVE) {
+        const int threads = tune && tune->block_threads > 0 ? tune->block_threads : 256;
+        if (threads % 64 || threads < 64 || threads > 1024)
+            return fp_set_error(FP_EINVAL, "block_threads %d must be a multiple of 64 in [64, 1024]", threads);
+        const uint8_t* base = static_cast<const uint8_t*>(p->dev);
+        NaiveArgs a{reinterpret_cast<const int64_t*>(base + h.table_offset),
+                    reinterpret_cast<const Node16*>(base + h.nodes_offset), X, ld, n_rows, votes, cls, h.n_trees,
+                    h.n_classes};
+        const size_t lds = (size_t)h.n_classes * threads * 4;
+        const bool use_lds = lds <= 32768;
+        const int blocks = (int)((n_rows + threads - 1) / threads);
+        if (use_lds)
+            hipLaunchKernelGGL(naive_kernel<true>, dim3(blocks), dim3(threads), lds, stream, a);
+        else
+            hipLaunchKernelGGL(naive_kernel<false>, dim3(blocks), dim3(threads), 0, stream, a);
+        return check_launch("naive_kernel");
+    }
+
+    Launch L;
+    rc = resolve_launch(p, tune, X, n_rows, ld, votes, cls, dp, &L);
+    if (rc) return rc;
+    const fp::JobDesc& j = L.j;
     if (j.atomic_votes) {
         rc = fp::launch_fill(votes, n_rows * h.n_classes, 0, stream);
         if (rc) return rc;
@@ -2315,12 +2337,38 @@ static int predict_impl(const fp_packed* p, const fp_tune* tune, const float* X,
         jp.group_base = pass * j.G;
         jp.accumulate = !j.atomic_votes && pass > 0;
         jp.cls = (!j.atomic_votes && pass == j.passes - 1) ? cls : nullptr;
-        rc = fp::launch_packed(jp, K, threads, blocks, stream);
+        rc = fp::launch_packed(jp, L.K, L.threads, L.blocks, stream);
         if (rc) return rc;
     }
     if (j.atomic_votes && cls) return fp::launch_argmax(votes, cls, n_rows, h.n_classes, stream);
     return FP_OK;
 }
+
+namespace fp {
+int default_launch(const fp_packed* p, const float* X, int64_t n_rows, int64_t ld, int32_t threads, int32_t cursors,
+                   int32_t* votes, fp_tune* out) {
+    int dev = -1;
+    int rc = current_device(&dev);
+    if (rc) return rc;
+    DeviceProps dp;
+    rc = device_props(dev, &dp);
+    if (rc) return rc;
+    fp_tune t{};
+    t.block_threads = threads;
+    t.cursors = cursors;
+    Launch L;
+    rc = resolve_launch(p, &t, X, n_rows, ld, votes, nullptr, dp, &L);
+    if (rc) return rc;
+    *out = fp_tune{};
+    out->rows_per_block = L.j.R;
+    out->cursors = L.K;
+    out->tree_groups = L.j.G;
+    out->block_threads = L.threads;
+    out->refill_lanes = L.j.refill_min;
+    if (p->hdr.layout < FP_LAYOUT_BLOCKED && L.threads <= 512) out->lds_bytes = L.j.lds_bytes;  // its share of a CU
+    return FP_OK;
+}
+}  // namespace fp
 
 // The launch parameters: the tune recorded for p's batch-size bucket
 // (fp_tune_launch, this process or the FP_TUNE_CACHE file), else p's own.

@@ -228,9 +228,22 @@ int search_launch(const fp_packed* p, const float* X, int64_t n_rows, int64_t ld
     std::vector<int> th_set = threads > 0 ? std::vector<int>{threads} : std::vector<int>{512, 1024};
     if (!blocks && threads <= 0) th_set.insert(th_set.begin(), 256);
     std::vector<int> k_set = cursors > 0 ? std::vector<int>{cursors} : blocks ? std::vector<int>{1} : std::vector<int>{1, 2, 4};
-    std::vector<int> r_set = blocks ? std::vector<int>{16, 32, 64, 96, 128, 256, 512} : std::vector<int>{16, 32, 64, 128};
+    std::vector<int> r_set = blocks ? std::vector<int>{16, 32, 64, 96, 128, 256, 512} : std::vector<int>{16, 32, 64, 128, 256};
     // a tile never needs more rows than the batch has
     r_set.erase(std::remove_if(r_set.begin() + 1, r_set.end(), [&](int r) { return r > 2 * n; }), r_set.end());
+    // and a small batch is spread over more tiles, up to two per CU
+    int dev = 0;
+    DeviceProps dp;
+    if ((rc = current_device(&dev)) || (rc = device_props(dev, &dp))) return rc;
+    for (int r = 8; r >= 1 && r * 2 * (int64_t)dp.cus >= n; r /= 2) r_set.insert(r_set.begin(), r);
+    // pass 0: the launch that fp_predict makes without a record, so that a
+    // record is never slower than none
+    {
+        fp_tune t;
+        rc = default_launch(p, X, n, ld, threads, cursors, static_cast<int32_t*>(votes.p), &t);
+        if (rc == FP_OK) rc = time_one(t);
+        if (rc && rc != FP_E2BIG) return rc;
+    }
     // pass 1: workgroup size, cursors, rows per workgroup
     for (int th : th_set)
         for (int k : k_set)
@@ -254,7 +267,8 @@ int search_launch(const fp_packed* p, const float* X, int64_t n_rows, int64_t ld
         if ((rc = time_one(t))) return rc;
     }
     const fp_tune p2 = best_t;
-    for (int g : {2, 4}) {
+    for (int g : {1, 2, 4, 8}) {
+        if (g == p2.tree_groups) continue;
         if (g > p->hdr.n_bins) break;
         fp_tune t = p2;
         t.tree_groups = g;
@@ -281,10 +295,7 @@ int search_launch(const fp_packed* p, const float* X, int64_t n_rows, int64_t ld
     // far and at one 1.5 and 3 times as large (what does not fit is skipped).
     // A plan's workgroups share one LDS budget, so plans (threads fixed)
     // skip it.
-    int dev = 0;
-    DeviceProps dp;
-    if (threads <= 0 && current_device(&dev) == FP_OK && device_props(dev, &dp) == FP_OK &&
-        dp.lds_per_block > (size_t)default_lds_block(dp)) {
+    if (threads <= 0 && dp.lds_per_block > (size_t)default_lds_block(dp)) {
         const fp_tune p4 = best_t;
         for (int grow : {2, 3, 6}) {
             fp_tune t = p4;
