@@ -56,7 +56,8 @@ constexpr int32_t kDone = INT32_MIN;
 // a refill adds two LDS round trips to it: later refills pay (40,000 rows x
 // 1,024 trees: at 16 lanes 342 us, at 48 308; 10^6 rows x 32 trees 245 and
 // 230); node steps are short (2,000 rows x 64 trees: 52 and 59 us).
-constexpr int kDefaultRefillLanes = 16, kDefaultRefillLanesBlocks = 48;
+constexpr int kDefaultRefillLanes = 16, kDefaultRefillLanesBlocks = 48, kDefaultRefillLanesDrift = 24;
+constexpr double kDriftDepth = 21.5;  // levels of an average walk (see resolve_job)
 // Rows of an automatic tile whose features stay in memory: the rows of a tile
 // are read from L1, which holds few (30,000 image rows x 128 trees: 16-row
 // tiles 340 us, 118-row ones 1420).
@@ -1936,7 +1937,20 @@ int resolve_job(const fp_packed* p, const fp_tune* t, const float* X, int64_t n_
     j->form = walk_form(h);
     j->block_bytes = j->form != kWalkNone ? walk_shape(j->form).bytes : h.block_bytes;
     if (t->refill_lanes < 0 || t->refill_lanes > 64) return fp_set_error(FP_EINVAL, "refill_lanes %d outside [0, 64]", t->refill_lanes);
-    j->refill_min = t->refill_lanes > 0 ? t->refill_lanes : blocks ? kDefaultRefillLanesBlocks : kDefaultRefillLanes;
+    // Explicit tiles of few rows, long walks and a forest of which L2 holds a
+    // small part: late refills let wavefronts drift apart over the trees, and
+    // workgroups no longer share what they fetch (2M rows x 448 trees of 24
+    // levels, 1.06 GB, 128-row tiles: 66.0 ms at 48 lanes, 50.8 at 24; 704
+    // trees, 192 rows: 102.6 and 74.2; 64 trees, 177 MB, 192 rows: 5.18 and
+    // 4.44).  For larger tiles 48 is the better one (448 trees, 256 rows, which
+    // full rounds make 253: 45.4 and 46.6; 512 rows: 35.3 and 38.7), and for
+    // walks of 19 levels (384 trees x 160 features, 96 rows: 5.8 and 6.3).
+    const bool drifts = blocks && cus > 0 && !auto_R && R < 224 && h.expected_depth > kDriftDepth &&
+                        (h.total_bytes - h.nodes_offset) / P > (int64_t(128) << 20);
+    j->refill_min = t->refill_lanes > 0 ? t->refill_lanes
+                    : drifts            ? kDefaultRefillLanesDrift
+                    : blocks            ? kDefaultRefillLanesBlocks
+                                        : kDefaultRefillLanes;
     // feature_lds: 1 force LDS staging, 2 force it in fp32, -1 read features
     // from memory, 0 automatic
     if (t->feature_lds < -1 || t->feature_lds > 2) return fp_set_error(FP_EINVAL, "feature_lds %d outside [-1, 2]", t->feature_lds);

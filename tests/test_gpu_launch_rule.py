@@ -1,7 +1,7 @@
 """Launches with some parameters given and the rest left to the rule: groups
 that would hold no bin, groups for idle CUs and for wide rows, smaller
 workgroups, features in memory, small shares of LDS.  Whole numbers: equal to
-the CPU checker's."""
+the oracle's."""
 import numpy as np
 import pytest
 
@@ -64,3 +64,18 @@ def test_wide_rows_and_many_classes(n_used, n_classes, layout):
     f = depth3_forest(T, [[(7 * t + k) % n_used for k in range(7)] for t in range(T)], n_classes, 0.1)
     rows = np.random.default_rng(1).random((600, f.n_features), dtype=np.float32)
     check(f, rows, oracle.predict(f, rows), layout, 16, [t for t in TUNES if t.get("lds_bytes") != 12000], (3, 600))
+
+
+@pytest.mark.parametrize("layout", [fp.FP_LAYOUT_BLOCKED, fp.FP_LAYOUT_CLUSTERED])
+def test_small_tiles_on_long_walks(layout):
+    """Over 128 MB of long walks: tiles of fewer than 224 rows refill earlier, passes of fewer bytes and larger tiles do not."""
+    rng = np.random.default_rng(12)
+    X = rng.random((600_000, 6), dtype=np.float32)
+    y = rng.integers(0, 2, len(X)).astype(np.int32)
+    f = synth.train_forest(X, y, n_trees=4, n_classes=2, mtry=2, max_depth=-1, bootstrap=True, seed=9)
+    f = synth.concat_forests([f] * 24)
+    rows = rng.random((1100, 6), dtype=np.float32)
+    p = check(f, rows, oracle.predict(f, rows), layout, 16,
+              [{"rows_per_block": r, "block_threads": t, "tree_passes": passes}
+               for r, t, passes in ((1, 512, 1), (96, 512, 1), (223, 1024, 1), (224, 1024, 1), (128, 512, 4), (0, 0, 1))], (1, 1100))
+    assert p.info["bytes"] > 140 << 20 and p.info["expected_depth"] > 21.5, p.info
