@@ -576,15 +576,19 @@ def vmem_ceiling(fp, torch, res, fetch_bytes):
     returns at all: the gather probe over a 16 KB working set (every CU's L1
     holds it) with 4 or 8 chains per lane.  The kernel's count is the
     training-distributed fetches per walk from the packed header times the
-    walks of a step; blocks served from LDS are included, so the fraction is
-    an upper estimate.  fetch_bytes: a block in its walk form on the device,
-    or the largest size the probe has below it."""
-    g = gather_ceiling(fp, torch, 16 << 10, fetch_bytes, chains=(4, 8))
+    walks of a step; blocks served from LDS, which the load path never sees,
+    are counted as well.  fetch_bytes: a block in its walk form on the device.
+    32-byte blocks, which the probe does not fetch whole, are taken as two
+    16-byte pieces against its 16-byte fetches: the load path is bound by
+    pieces (0.8 cycles for one, 1.5 for two of a block, 2.2 for three)."""
+    pieces = 1 if fetch_bytes in (16, 48, 64) else fetch_bytes // 16
+    g = gather_ceiling(fp, torch, 16 << 10, fetch_bytes if pieces == 1 else 16, chains=(4, 8))
+    ceiling = g["fetches_per_s"] / pieces
     walks = res["n_rows"] * res["n_trees"]
     kernel = res["expected_fetches_per_walk"] * walks / (res["ms_per_step"] / 1e3)
-    return {"probe_block_fetches_per_s": g["fetches_per_s"], "probe_working_set_bytes": g["working_set_bytes"],
+    return {"probe_block_fetches_per_s": ceiling, "probe_working_set_bytes": g["working_set_bytes"],
             "probe_chains_per_lane": g["chains_per_lane"], "fetch_bytes": fetch_bytes,
-            "kernel_block_fetches_per_s": kernel, "frac": kernel / g["fetches_per_s"]}
+            "kernel_block_fetches_per_s": kernel, "frac": kernel / ceiling}
 
 
 def probes(args, fp, synth, torch):
@@ -696,7 +700,7 @@ def headline(args, fp, torch, np, presets, tab_w):
             **{k: res[k] for k in ("n_rows", "n_trees", "n_features", "n_classes", "internal_nodes", "layout",
                                    "bin_size", "interleave_depth", "tune", "packed_bytes",
                                    "expected_fetches_per_walk")},
-            "compare": "fp32 x <= fp32 threshold (64-byte clustered blocks)",
+            "compare": "fp32 x <= fp32 threshold (64-byte clustered blocks, 48 bytes on the device)",
         },
         "naive": res["naive"],
         "speedup_vs_naive": res["speedup_vs_naive"],
@@ -789,7 +793,7 @@ def main():
             r["compare"] = ("fp16: rows staged in LDS rounded toward +inf, every threshold exact in fp16 "
                             "(48-byte clustered blocks, 32 bytes on the device); decides every x <= t exactly as fp32")
             r["roofline"] = roofline(r, "image")
-            r["vmem_ceiling"] = vmem_ceiling(fp, torch, r, 16)
+            r["vmem_ceiling"] = vmem_ceiling(fp, torch, r, r["block_bytes_per_fetch"])
             torch.cuda.empty_cache()
         elif leg == "batched":
             r = leg_batched(args, fp, synth, torch, np, 8 if args.lite else 64)
