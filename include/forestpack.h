@@ -229,7 +229,9 @@ int fp_packed_load(const char *path, fp_packed **out);
  * `stream`.  p remembers dev and the current device; predictions read it.
  * Block layouts are put into a form made for the walk there (same splits,
  * fewer bytes; inside info.bytes): the device copy is for predictions only,
- * the packed format is what the host functions return.
+ * the packed format is what the host functions return.  dev is rewritten
+ * while it is put into that form: no prediction in flight may read it then,
+ * also when it already holds the same forest.
  * Errors: FP_EINVAL (null, misaligned), FP_E2BIG (cap too small), FP_EHIP.
  */
 int fp_packed_upload(fp_packed *p, void *dev, size_t cap, void *stream);
