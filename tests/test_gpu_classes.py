@@ -1,6 +1,6 @@
 """Classes taken from a tile's votes, four at a time and the rest one by one:
 class counts around multiples of four, many ties (the lowest class wins).
-Equal to the CPU checker's."""
+Equal to the oracle's."""
 import numpy as np
 import pytest
 

@@ -1,7 +1,7 @@
 """The work counters of batched launches are kept between runs (plans) or
 copied with each call: runs that overlapped on two streams leave nothing
 behind that a later run, alone, would suffer from.  Whole numbers: equal to
-the CPU checker's."""
+the oracle's."""
 import numpy as np
 import pytest
 import torch

@@ -1,8 +1,8 @@
 """PACKED buffers whose alignment gaps (node slots behind a bin that no
 reference reaches) hold anything at all: the verifier accepts them, and a walk
 that loads a node together with the slot behind it takes nothing from a gap,
-whatever feature it names.  Votes are whole numbers: equal to the CPU
-checker's."""
+whatever feature it names.  Votes are whole numbers: equal to the
+oracle's."""
 import numpy as np
 import pytest
 

@@ -1,7 +1,7 @@
 """What the no-alloc call's fixed scratch has to hold: a full table of 4,096
 jobs with 11,092 work items, and the two work lists of block-layout and
 node-layout jobs where one list over both would fit.  Whole numbers: equal to
-the CPU checker's."""
+the oracle's."""
 import numpy as np
 import pytest
 import torch

@@ -1,7 +1,7 @@
 """PACKED nodes fetched in pairs: forests on both sides of the depths from
 which they are (7 levels below the bin tops for busy launches, 8.5 for small
 ones), top regions staged whole and in part, features in LDS and in memory,
-one walk per lane to four.  Whole numbers: equal to the CPU checker's."""
+one walk per lane to four.  Whole numbers: equal to the oracle's."""
 import numpy as np
 import pytest
 

@@ -1,6 +1,6 @@
 """Plans and no-alloc calls whose tiles are left to the library, over workgroup
 sizes: 16 to 64 rows, 64 tiles of 1,024 threads or more.  Whole numbers: equal
-to the CPU checker's."""
+to the oracle's."""
 import numpy as np
 import pytest
 import torch

@@ -1,6 +1,6 @@
 """The launch search on small and ordinary batches of every layout: it starts
 from the launch that fp_predict makes without a record, and goes down to tiles
-of one row.  What it records predicts as the CPU checker does."""
+of one row.  What it records predicts as the oracle does."""
 import numpy as np
 import pytest
 

@@ -1,8 +1,8 @@
 """Walks of many blocks in every walk form and in both host forms, with part
 of the blocks in LDS, none, features in LDS and in memory, one forest at a
 time and in a batched launch; and, on the CPU, the form that each header
-takes on both sides of every limit.  Whole numbers: equal to the CPU
-checker's."""
+takes on both sides of every limit.  Whole numbers: equal to the
+oracle's."""
 import os
 import subprocess
 
