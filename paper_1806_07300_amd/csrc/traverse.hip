@@ -1533,10 +1533,15 @@ __global__ __launch_bounds__(1024, (MinWaves<K, KIND>::value)) void packed_kerne
     const int group = j.group_base + (int)(blockIdx.x % j.G);
     const int blocks_per_group = gridDim.x / j.G;
     int tile = blockIdx.x / j.G;
-    const float4 pre = prefetch_quad<FMODE>(j, tile);
+    // Single nodes with four cursors have no registers for the first quad (five
+    // spilled: 1M tabular rows x 16 trees, 256-row tiles 1.69 ms with it, 1.51
+    // without; 1M image rows x 128 trees, 32-row tiles 14.2 and 10.9)
+    constexpr bool kPrefetch = K < 4 || KIND != kKindPacked;
+    float4 pre = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+    if constexpr (kPrefetch) pre = prefetch_quad<FMODE>(j, tile);
     const int nt = stage_group<KIND>(j, group, smem);
     if (nt == 0) return;  // uniform per block
-    bool first = true;
+    bool first = kPrefetch;
     for (; tile < j.n_tiles; tile += blocks_per_group) {
         stage_kind<FMODE, KIND>(j, tile, smem, pre, first);
         first = false;

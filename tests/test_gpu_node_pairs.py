@@ -44,3 +44,23 @@ def test_both_sides_of_the_depths(forest, below, n, cursors):
     fp.fp_predict_batched_noalloc([(p, X, votes, None)], cursors=cursors)
     torch.cuda.synchronize()
     assert np.array_equal(votes.cpu().numpy(), want[0][:n])
+
+
+@pytest.mark.parametrize("cursors", [2, 4, 8])
+@pytest.mark.parametrize("n_features,pad", [(8, 0), (9, 3), (10, 0), (40, 4)])
+def test_first_and_later_tiles(cursors, n_features, pad):
+    """A workgroup's first tile, of which some kernels fetch the first quads ahead, and those after it."""
+    import torch
+    rng = np.random.default_rng(n_features)
+    X = rng.random((900, n_features), dtype=np.float32)
+    f = synth.train_forest(X, rng.integers(0, 5, 900).astype(np.int32), n_trees=7, n_classes=5, mtry=3, max_depth=-1,
+                           bootstrap=True, seed=6)
+    rows = rng.random((9_001, n_features + pad), dtype=np.float32)
+    want = oracle.predict(f, np.ascontiguousarray(rows[:, :n_features]))
+    Xd = torch.from_numpy(rows).cuda()[:, :n_features]
+    p = fp.fp_pack_forest(f, layout=fp.FP_LAYOUT_PACKED, bin_size=3, interleave_depth=3)
+    fp.fp_packed_upload(p)
+    for tune in ({"rows_per_block": 4}, {"rows_per_block": 7, "block_threads": 64}, {"rows_per_block": 64, "block_threads": 1024}):
+        v, c = fp.fp_predict_tuned(p, dict(tune, cursors=cursors), Xd)
+        torch.cuda.synchronize()
+        assert np.array_equal(v.cpu().numpy(), want[0]) and np.array_equal(c.cpu().numpy(), want[1]), tune
